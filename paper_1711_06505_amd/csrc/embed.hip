@@ -289,7 +289,13 @@ __global__ __launch_bounds__(kThreads) void l1_fwd_f32(const float *__restrict__
 constexpr int kSkThreads = 512;
 constexpr int kSkBN = 256;
 constexpr int kSkNB = kSkBN / 64;                         // 32-column MFMA blocks per wave: 4
-constexpr int kSkMinIters = 32;                           // smallest share worth a worker
+// Smallest share worth a worker, in K stages.  A shorter share ends the layer
+// sooner and leaves the tail one more partial tile per row to add; forward at
+// 400 unique rows of the 4096-256-64-12 net with shares of 2 / 4 / 8 / 16 / 32:
+// bf16 40.3 / 31.4 / 29.1 / 32.9 / 48.1 us, float32 56.7 / 51.2 / 59.6 / 85.7 /
+// 148.5 us, split float32 59.1 / 50.8 / 53.1 / 68.2 / 104.0 us.
+template <typename TT>
+constexpr int sk_min_stages() { return sizeof(TT) == 2 ? 8 : 4; }
 
 template <int BM_, int R_, int RB_>
 struct SkShape {
@@ -338,18 +344,51 @@ struct SkPlan {
     __device__ int owner(int64_t it) const { return (int)(((it + 1) * g - 1) / total); }
 };
 
+// Workers in use.  With p whole shares per tile (p as many as the workers
+// allow, none shorter than sk_min_stages) no share crosses a tile boundary:
+// every tile has p partial tiles in place of up to p + 2.  That is taken when
+// p is the most a tile may have, or when it leaves at most 1/4 (bf16) or 1/16
+// (float32, bound by its MFMAs) of the workers idle; otherwise all G workers
+// take equal shares.  Forward at 12900 rows in bf16, 202 workers in place of
+// 256: 59.7 against 65.2 us (layer 41.8 / 40.7, tail 22.0 / 28.5).
+template <typename TT>
 __device__ __forceinline__ SkPlan sk_plan(int n_u, int H, int F, int G, int bk, int bm)
 {
     SkPlan p;
     p.n_u = n_u;
     p.n_cb = H / kSkBN;
     p.S = F / bk;
-    const int64_t tiles = (int64_t)((n_u + bm - 1) / bm) * p.n_cb;
-    p.total = tiles * p.S;
-    const int64_t want = (p.total + kSkMinIters - 1) / kSkMinIters;
-    p.g = (int)(want < G ? want : G);
-    if (p.g < 1) p.g = 1;
+    const int tiles = ((n_u + bm - 1) / bm) * p.n_cb;
+    p.total = (int64_t)tiles * p.S;
+    p.g = G;
+    if (tiles <= G) {
+        const int most = p.S > sk_min_stages<TT>() ? p.S / sk_min_stages<TT>() : 1;
+        const int per = G / tiles < most ? G / tiles : most;
+        constexpr int idle = sizeof(TT) == 2 ? 4 : 16;
+        if (per == most || per * tiles >= G - G / idle) p.g = per * tiles;
+    }
     return p;
+}
+
+// The worker of this block, or -1: workers with consecutive shares sit on one
+// XCD (blocks go round-robin over the 8), every XCD taking an eighth of them
+// however many are in use.
+__device__ __forceinline__ int sk_worker(const SkPlan &P)
+{
+    const int per_xcd = (P.g + 7) >> 3, k = blockIdx.x >> 3;
+    const int w = (blockIdx.x & 7) * per_xcd + k;
+    return k < per_xcd && w < P.g ? w : -1;
+}
+
+// Float offset of (row, unit) in a partial tile: quads of units outermost, so
+// that the 32 rows a wave holds one quad of are 512 contiguous bytes both
+// where the layer stores its accumulators and where the tail reads them (row
+// by row the tail's loads took 16 bytes of 32 lines each: its time with eight
+// shares per tile 24.2 us in bf16, 19.9 so).
+template <int BM>
+__device__ __forceinline__ int sk_piece_off(int row, int unit)
+{
+    return ((unit >> 2) * BM + row) * 4;
 }
 
 // src[q] are byte pointers; k0b is the stage's byte offset within a row
@@ -395,14 +434,14 @@ __device__ __forceinline__ void sk_compute(const float *slot, v16f (*acc)[kSkNB]
                     for (int nb = 0; nb < kSkNB; ++nb) {
                         const float bv[4] = {__uint_as_float(b[g][nb].x), __uint_as_float(b[g][nb].y),
                                              __uint_as_float(b[g][nb].z), __uint_as_float(b[g][nb].w)};
-                        acc[mb][nb] = mfma_f32(av[e], bv[e], acc[mb][nb]);
+                        acc[mb][nb] = mfma_f32(bv[e], av[e], acc[mb][nb]);
                     }
             }
         } else {
 #pragma unroll
             for (int mb = 0; mb < K::MB; ++mb)
 #pragma unroll
-                for (int nb = 0; nb < kSkNB; ++nb) acc[mb][nb] = mfma_bf16(a[g][mb], b[g][nb], acc[mb][nb]);
+                for (int nb = 0; nb < kSkNB; ++nb) acc[mb][nb] = mfma_bf16(b[g][nb], a[g][mb], acc[mb][nb]);
         }
     }
     // group 0's reads first, then (reads of g+1, MFMAs of g)
@@ -414,54 +453,73 @@ __device__ __forceinline__ void sk_compute(const float *slot, v16f (*acc)[kSkNB]
     }
 }
 
-// Epilogue of a stream-K segment.  whole: the segment covered the tile's full
-// K, so H1 = act(acc + b1) is written (b1 alone for a row whose ID is out of
-// range; keep_z keeps the pre-activation); otherwise acc goes to this
-// worker's partial tile `piece` (row-major, kSkBN floats per row).
+// Epilogue of a stream-K segment.  The products have the W1 rows as their
+// first operand, so a lane holds one image row and runs of four consecutive
+// units.  whole: the segment covered the tile's full K, so H1 = act(acc + b1)
+// is written (b1 alone for a row whose ID is out of range; keep_z keeps the
+// pre-activation); otherwise acc goes to this worker's partial tile `piece`
+// (sk_piece_off: 512 contiguous bytes per store of 32 lanes).
 template <int MB>
 __device__ __forceinline__ void sk_store(const v16f (&acc)[MB][kSkNB], bool whole, const int *rid, int m0, int n0,
                                          int n_u, int H, const float *__restrict__ b1, int keep_z,
                                          float *__restrict__ H1, uint16_t *__restrict__ H1b,
                                          uint16_t *__restrict__ H1lo, float *__restrict__ piece, int lane, int wave)
 {
-    const int wm = wave >> 1, wn = wave & 1, r32 = lane & 31;
-    // this lane's rows are rl0 + 32 mb + 8 (j / 4) + j % 4, its columns
-    // c0 + 32 nb (MFMA accumulator layout)
-    const int rl0 = wm * 32 * MB + 4 * (lane >> 5);
-    const int c0 = wn * (kSkBN / 2) + r32;
+    const int wm = wave >> 1, wn = wave & 1, h = lane >> 5;
+    // this lane's rows are rl0 + 32 mb, its units c0 + 32 nb + 8 q + {0..3}
+    const int rl0 = wm * 32 * MB + (lane & 31);
+    const int c0 = wn * (kSkBN / 2) + 4 * h;
     if (whole) {
-        float bias[kSkNB];
 #pragma unroll
-        for (int nb = 0; nb < kSkNB; ++nb) bias[nb] = b1[n0 + c0 + nb * 32];
+        for (int nb = 0; nb < kSkNB; ++nb) {
+            float4 bias[4];
 #pragma unroll
-        for (int mb = 0; mb < MB; ++mb)
+            for (int q = 0; q < 4; ++q) {
+                const float *bp = b1 + n0 + c0 + nb * 32 + 8 * q;        // (b1 may start anywhere)
+                bias[q] = make_float4(bp[0], bp[1], bp[2], bp[3]);
+            }
 #pragma unroll
-            for (int j = 0; j < 16; ++j) {
-                const int r = rl0 + mb * 32 + 8 * (j >> 2) + (j & 3);
+            for (int mb = 0; mb < MB; ++mb) {
+                const int r = rl0 + mb * 32;
                 if (m0 + r >= n_u) continue;
                 const bool ok = rid[r] >= 0;
-                const size_t o = (size_t)(m0 + r) * H + n0 + c0;
 #pragma unroll
-                for (int nb = 0; nb < kSkNB; ++nb) {
-                    const float z0 = ok ? acc[mb][nb][j] + bias[nb] : bias[nb];
-                    const float z = keep_z ? z0 : fmaxf(z0, 0.f);
-                    if (H1) H1[o + nb * 32] = z;
+                for (int q = 0; q < 4; ++q) {
+                    const float bq[4] = {bias[q].x, bias[q].y, bias[q].z, bias[q].w};
+                    float z[4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const float z0 = ok ? acc[mb][nb][4 * q + e] + bq[e] : bq[e];
+                        z[e] = keep_z ? z0 : fmaxf(z0, 0.f);
+                    }
+                    const size_t o = (size_t)(m0 + r) * H + n0 + c0 + nb * 32 + 8 * q;
+                    if (H1) *(float4 *)(H1 + o) = make_float4(z[0], z[1], z[2], z[3]);
                     if (H1b) {
-                        const uint16_t hi = ams_f32_to_bf16(z);
-                        H1b[o + nb * 32] = hi;
-                        if (H1lo) H1lo[o + nb * 32] = ams_f32_to_bf16(z - ams_bf16_to_f32(hi));
+                        uint16_t hi[4], lo[4];
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            hi[e] = ams_f32_to_bf16(z[e]);
+                            lo[e] = ams_f32_to_bf16(z[e] - ams_bf16_to_f32(hi[e]));
+                        }
+                        *(uint2 *)(H1b + o) =
+                            make_uint2(hi[0] | ((uint32_t)hi[1] << 16), hi[2] | ((uint32_t)hi[3] << 16));
+                        if (H1lo)
+                            *(uint2 *)(H1lo + o) =
+                                make_uint2(lo[0] | ((uint32_t)lo[1] << 16), lo[2] | ((uint32_t)lo[3] << 16));
                     }
                 }
             }
+        }
     } else {
-        float *pp = piece + rl0 * kSkBN + c0;
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-            for (int j = 0; j < 16; ++j)
+            for (int nb = 0; nb < kSkNB; ++nb)
 #pragma unroll
-                for (int nb = 0; nb < kSkNB; ++nb)
-                    pp[(mb * 32 + 8 * (j >> 2) + (j & 3)) * kSkBN + nb * 32] = acc[mb][nb][j];
+                for (int q = 0; q < 4; ++q)
+                    *(float4 *)(piece + sk_piece_off<128 * MB>(rl0 + mb * 32, c0 + nb * 32 + 8 * q)) =
+                        make_float4(acc[mb][nb][4 * q], acc[mb][nb][4 * q + 1], acc[mb][nb][4 * q + 2],
+                                    acc[mb][nb][4 * q + 3]);
     }
 }
 
@@ -487,10 +545,9 @@ __global__ __launch_bounds__(kSkThreads) void l1sk(const TT *__restrict__ T, int
 
     const int n_u = min(*n_uniq_p, cap);
     if (n_u <= 0) return;
-    const SkPlan P = sk_plan(n_u, H, F, G, BK, K::BM);
-    // workers with consecutive shares sit on one XCD (blocks go round-robin)
-    const int w = (blockIdx.x & 7) * (G >> 3) + (blockIdx.x >> 3);
-    if (w >= P.g) return;
+    const SkPlan P = sk_plan<TT>(n_u, H, F, G, BK, K::BM);
+    const int w = sk_worker(P);
+    if (w < 0) return;
     const int64_t it1 = P.it0(w + 1);
     const int t = threadIdx.x, lane = ams_lane(), wave = t / AMS_WAVE;
     const int S = P.S;
@@ -955,12 +1012,12 @@ __device__ __forceinline__ void x3_compute(const float *slot, v16f (&acc)[1][kSk
 #pragma unroll
         for (int nb = 0; nb < kSkNB; ++nb) {
             v16f c = acc[0][nb];
-            c = mfma_bf16(ah, bh[nb], c);
-            c = mfma_bf16(ah, bm[nb], c);
-            c = mfma_bf16(am, bh[nb], c);
-            c = mfma_bf16(ah, bl[nb], c);
-            c = mfma_bf16(al, bh[nb], c);
-            c = mfma_bf16(am, bm[nb], c);
+            c = mfma_bf16(bh[nb], ah, c);
+            c = mfma_bf16(bm[nb], ah, c);
+            c = mfma_bf16(bh[nb], am, c);
+            c = mfma_bf16(bl[nb], ah, c);
+            c = mfma_bf16(bh[nb], al, c);
+            c = mfma_bf16(bm[nb], am, c);
             acc[0][nb] = c;
         }
     }
@@ -981,9 +1038,9 @@ __global__ __launch_bounds__(kSkThreads) void l1sk_x3(const float *__restrict__ 
 
     const int n_u = min(*n_uniq_p, cap);
     if (n_u <= 0) return;
-    const SkPlan P = sk_plan(n_u, H, F, G, X3::BK, X3::BM);
-    const int w = (blockIdx.x & 7) * (G >> 3) + (blockIdx.x >> 3);
-    if (w >= P.g) return;
+    const SkPlan P = sk_plan<float>(n_u, H, F, G, X3::BK, X3::BM);
+    const int w = sk_worker(P);
+    if (w < 0) return;
     const int64_t it1 = P.it0(w + 1);
     const int t = threadIdx.x, lane = ams_lane(), wave = t / AMS_WAVE;
     const int S = P.S;
@@ -1322,7 +1379,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
             // the chunk's 32 rows lie in one row tile (BM is a multiple of
             // 32): the plan is the same for the whole wave, worked out on the
             // scalar unit
-            const SkPlan P = sk_plan(n_u, H, F, G, sk_bk, Sk<float>::BM);
+            const SkPlan P = sk_plan<float>(n_u, H, F, G, sk_bk, Sk<float>::BM);
             const int tile = __builtin_amdgcn_readfirstlane((c0 / Sk<float>::BM) * P.n_cb + cb);
             wa = __builtin_amdgcn_readfirstlane(P.owner((int64_t)tile * P.S));
             wb = __builtin_amdgcn_readfirstlane(P.owner((int64_t)(tile + 1) * P.S - 1));
@@ -1333,12 +1390,13 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
         if (split) {
             // tile cut by share boundaries: the two waves of this K half each
             // add up half of its 32-k blocks, the pieces in K order with the
-            // loads of up to three shares in flight together (a tile spans at
-            // most three shares; more are looped), apply b1 and the
-            // activation, store H1 and pass the rows on through LDS
+            // loads of up to three shares in flight together (a large batch's
+            // tile spans at most three shares, a small one's up to
+            // S / sk_min_stages), apply b1 and the activation, store H1 and
+            // pass the rows on through LDS
             const int id = uniq[rowc];
             const int rl = rowc % Sk<float>::BM;
-            const float *pr = pbuf + (size_t)rl * kSkBN + (cbase - cb * kSkBN) + 16 * h;
+            const float *pr = pbuf + sk_piece_off<Sk<float>::BM>(rl, cbase - cb * kSkBN + 16 * h);
             float4 v[3][KH][4];
             // (a 32-k block past the half reloads block 0: every load of a
             // share is issued unconditionally; such blocks are never used)
@@ -1349,7 +1407,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
 #pragma unroll
                     for (int q = 0; q < 4; ++q) {
                         const int kb = nb * KH + i;
-                        x[i][q] = *(const float4 *)(pw + (kb < nkb ? kb * 32 : 0) + 4 * q);
+                        x[i][q] = *(const float4 *)(pw + sk_piece_off<Sk<float>::BM>(0, (kb < nkb ? kb * 32 : 0) + 4 * q));
                     }
             };
             auto add = [&](float4 (&acc4)[KH][4], const float4 (&x)[KH][4]) {
@@ -1363,20 +1421,18 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
                         acc4[i][q].w += x[i][q].w;
                     }
             };
-            load_share(wa, slot_a, v[0]);
-            if (wa + 1 <= wb) load_share(wa + 1, 0, v[1]);
-            if (wa + 2 <= wb) load_share(wa + 2, 0, v[2]);
             float4 sum[KH][4];
 #pragma unroll
             for (int i = 0; i < KH; ++i)
 #pragma unroll
                 for (int q = 0; q < 4; ++q) sum[i][q] = make_float4(0.f, 0.f, 0.f, 0.f);
-            add(sum, v[0]);
-            if (wa + 1 <= wb) add(sum, v[1]);
-            if (wa + 2 <= wb) add(sum, v[2]);
-            for (int w = wa + 3; w <= wb; ++w) {
-                load_share(w, 0, v[0]);
+            for (int w = wa; w <= wb; w += 3) {
+                load_share(w, w == wa ? slot_a : 0, v[0]);
+                if (w + 1 <= wb) load_share(w + 1, 0, v[1]);
+                if (w + 2 <= wb) load_share(w + 2, 0, v[2]);
                 add(sum, v[0]);
+                if (w + 1 <= wb) add(sum, v[1]);
+                if (w + 2 <= wb) add(sum, v[2]);
             }
             const bool ok = id >= 0 && (int64_t)id < n_rows;
 #pragma unroll
@@ -1898,7 +1954,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
 
     const bool relu2 = (L == 3 && !PR) || (L == 2 && final_relu);
     using K = Sk<uint16_t>;
-    const SkPlan P = sk_plan(n_u, H, F, G, sk_bk<uint16_t>(), K::BM);
+    const SkPlan P = sk_plan<uint16_t>(n_u, H, F, G, sk_bk<uint16_t>(), K::BM);
     for (int c0 = blockIdx.x * 32; c0 < n_u; c0 += gridDim.x * 32) {
         const int row = c0 + r32;
         const bool live = row < n_u;
@@ -1912,39 +1968,46 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
             const int id = uniq[rowc];
             const bool id_ok = id >= 0 && (int64_t)id < n_rows;
             const int rl = rowc % K::BM;
-            const bool has1 = wa + 1 <= wb, has2 = wa + 2 <= wb;
-            const float *pw0 = pbuf + ((size_t)wa * 2 + slot_a) * K::TILE + rl * kSkBN;
-            const float *pw1 = has1 ? pbuf + ((size_t)(wa + 1) * 2) * K::TILE + rl * kSkBN : pw0;
-            const float *pw2 = has2 ? pbuf + ((size_t)(wa + 2) * 2) * K::TILE + rl * kSkBN : pw0;
-            float4 pv[3][4][2];
+            // the shares in K order, the loads of up to three of them in
+            // flight together
+            float x4[4][8];
 #pragma unroll
-            for (int s4 = 0; s4 < 4; ++s4) {
-                const int k0 = 64 * q + 16 * s4 + 8 * h;
-                pv[0][s4][0] = *(const float4 *)(pw0 + k0);
-                pv[0][s4][1] = *(const float4 *)(pw0 + k0 + 4);
-                pv[1][s4][0] = *(const float4 *)(pw1 + k0);
-                pv[1][s4][1] = *(const float4 *)(pw1 + k0 + 4);
-                pv[2][s4][0] = *(const float4 *)(pw2 + k0);
-                pv[2][s4][1] = *(const float4 *)(pw2 + k0 + 4);
+            for (int s4 = 0; s4 < 4; ++s4)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) x4[s4][e] = 0.f;
+            for (int w = wa; w <= wb; w += 3) {
+                const bool has1 = w + 1 <= wb, has2 = w + 2 <= wb;
+                const float *pw0 = pbuf + ((size_t)w * 2 + (w == wa ? slot_a : 0)) * K::TILE + rl * 4;
+                const float *pw1 = has1 ? pbuf + ((size_t)(w + 1) * 2) * K::TILE + rl * 4 : pw0;
+                const float *pw2 = has2 ? pbuf + ((size_t)(w + 2) * 2) * K::TILE + rl * 4 : pw0;
+                float4 pv[3][4][2];
+#pragma unroll
+                for (int s4 = 0; s4 < 4; ++s4) {
+                    const int k0 = 64 * q + 16 * s4 + 8 * h;
+                    pv[0][s4][0] = *(const float4 *)(pw0 + sk_piece_off<K::BM>(0, k0));
+                    pv[0][s4][1] = *(const float4 *)(pw0 + sk_piece_off<K::BM>(0, k0 + 4));
+                    pv[1][s4][0] = *(const float4 *)(pw1 + sk_piece_off<K::BM>(0, k0));
+                    pv[1][s4][1] = *(const float4 *)(pw1 + sk_piece_off<K::BM>(0, k0 + 4));
+                    pv[2][s4][0] = *(const float4 *)(pw2 + sk_piece_off<K::BM>(0, k0));
+                    pv[2][s4][1] = *(const float4 *)(pw2 + sk_piece_off<K::BM>(0, k0 + 4));
+                }
+#pragma unroll
+                for (int s4 = 0; s4 < 4; ++s4) {
+                    float (&x)[8] = x4[s4];
+#pragma unroll
+                    for (int pi = 0; pi < 3; ++pi) {
+                        if (pi == 0 || (pi == 1 ? has1 : has2)) {
+                            const float4 v0 = pv[pi][s4][0], v1 = pv[pi][s4][1];
+                            x[0] += v0.x; x[1] += v0.y; x[2] += v0.z; x[3] += v0.w;
+                            x[4] += v1.x; x[5] += v1.y; x[6] += v1.z; x[7] += v1.w;
+                        }
+                    }
+                }
             }
 #pragma unroll
             for (int s4 = 0; s4 < 4; ++s4) {
                 const int k0 = 64 * q + 16 * s4 + 8 * h;
-                float x[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int pi = 0; pi < 3; ++pi) {
-                    if (pi == 0 || (pi == 1 ? has1 : has2)) {
-                        const float4 v0 = pv[pi][s4][0], v1 = pv[pi][s4][1];
-                        x[0] += v0.x; x[1] += v0.y; x[2] += v0.z; x[3] += v0.w;
-                        x[4] += v1.x; x[5] += v1.y; x[6] += v1.z; x[7] += v1.w;
-                    }
-                }
-                for (int w = wa + 3; w <= wb; ++w) {     // (a tile spans at most 3 shares)
-                    const float *pc = pbuf + ((size_t)w * 2) * K::TILE + rl * kSkBN + k0;
-                    const float4 v0 = *(const float4 *)pc, v1 = *(const float4 *)(pc + 4);
-                    x[0] += v0.x; x[1] += v0.y; x[2] += v0.z; x[3] += v0.w;
-                    x[4] += v1.x; x[5] += v1.y; x[6] += v1.z; x[7] += v1.w;
-                }
+                float (&x)[8] = x4[s4];
                 const float4 c0v = *(const float4 *)&B1s[k0], c1v = *(const float4 *)&B1s[k0 + 4];
                 const float bb[8] = {c0v.x, c0v.y, c0v.z, c0v.w, c1v.x, c1v.y, c1v.z, c1v.w};
 #pragma unroll
