@@ -141,389 +141,521 @@ __host__ __device__ inline int net_part_size(const CtrArgs &a)
     return n;
 }
 
-// Parts of a layer split over threads: forward P * kCtrBS * O, backward-data
-// P * kCtrBS * K (P is chosen as in ctr_dense_fwd / ctr_dense_bwd_data).
-__host__ __device__ inline int ctr_fwd_parts(int K, int O)
+// The nets' layers run on float32 MFMA (v_mfma_f32_16x16x4_f32): the block's
+// 16 samples are one side of every tile.  Lane l holds row l % 16 of the
+// first operand and column l % 16 of the second, each at k = l / 16, and of
+// the 16 x 16 result rows 4 (l / 16) .. + 3 of column l % 16.  Which k a step
+// takes is free as long as both operands agree, so four steps take
+// k = 16 g + 4 (l / 16) + e, e = 0..3: one 16-byte read per operand feeds
+// them.  Where a lane's quad runs along the result's columns instead (the W
+// rows of the backward, a layer's input in the weight gradient), its four
+// elements belong to four tiles whose columns are 4 (l % 16) + e: one read
+// feeds four tiles, and the results are stored as 16-byte quads.
+// What bounds these kernels: a dozen dependent phases of a barrier, an L2 round
+// trip and a few tens of MFMAs per wave (counters on the 72-200-80-2 net: a
+// wave waits half of its time and issues a third of it), and last the partial
+// rows' stores (31 MB at 4096 samples, 8 us).  4096 samples with PReLU, kernel
+// trace: that net 55 us with the layers as vector FMA loops, 41 us so; a pair
+// of 48-64-32 towers 57 and 27 us (side by side, four waves each).
+typedef float f4 __attribute__((ext_vector_type(4)));
+typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));   // any float address
+
+__device__ __forceinline__ f4 mfma4(float a, float b, f4 c)
 {
-    int P = kCtrThreads / O;
-    if (P < 1) P = 1;
-    if (P > (K + 15) / 16) P = (K + 15) / 16;
-    return P;
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
 
-__host__ __device__ inline int ctr_bwd_parts(int K, int O)
+// Barrier that orders LDS accesses only: global loads issued ahead of it and
+// the partial row's stores stay in flight.
+__device__ __forceinline__ void lds_barrier()
 {
-    int P = kCtrThreads / K;
-    if (P < 1) P = 1;
-    if (P > (O + 7) / 8) P = (O + 7) / 8;
-    return P;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// Reads one word of each of the first N 64-byte lines of the kernel's
+// arguments, all in flight together: the layers come to them one by one, and
+// each line's first read is a miss to memory.
+template <int N>
+__device__ __forceinline__ void net_args_touch()
+{
+    typedef const __attribute__((address_space(4))) int kint;
+    kint *p = (kint *)__builtin_amdgcn_kernarg_segment_ptr();
+    int x[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) x[i] = p[16 * i];
+#pragma unroll
+    for (int i = 0; i < N; ++i) asm volatile("" ::"s"(x[i]));
+}
+
+// LDS row length of a layer w wide: whole quads (the pad columns are zero),
+// and an odd number of them, so that 16 rows' quads fall in distinct banks.
+__host__ __device__ inline int net_ld(int w) { return 4 * (((w + 3) / 4) | 1); }
+
+// A row's quad at column k for a group of 16 that may pass the row's end at w:
+// zero there.
+__device__ __forceinline__ f4 net_quad(const float *row, int k, int w)
+{
+    const bool in = k < w;
+    const f4 v = *(const f4 *)(row + (in ? k : 0));
+    return in ? v : (f4){0.f, 0.f, 0.f, 0.f};
+}
+
+// Data gradient of a layer K wide into O by nw waves: blocks of 64 inputs
+// times parts of the contraction over O (in groups of 16).
+__host__ __device__ inline int net_kblocks(int K) { return (K + 63) / 64; }
+__host__ __device__ inline int net_bwd_parts(int K, int O, int nw)
+{
+    const int p = nw / net_kblocks(K), groups = (O + 15) / 16;
+    return p < 1 ? 1 : p < groups ? p : groups;
+}
+
+// LDS of one net for a block of kCtrBS samples: act (every layer's
+// activations, the input fields first), grd (the loss gradient of each
+// act[l]; with PReLU a hidden layer's slot holds its pre-activations between
+// the forward and the backward) and the parts of the data gradients.
+
+// net_off: where layer l's activations (and gradients) start.
+__host__ __device__ inline int net_off(const CtrArgs &a, int l)
+{
+    int n = 0;
+    for (int x = 0; x < l; ++x) n += kCtrBS * net_ld(a.dims[x]);
+    return n;
+}
+
+__host__ __device__ inline int net_act_floats(const CtrArgs &a) { return net_off(a, a.L + 1); }
+
+__host__ __device__ inline int net_scr_floats(const CtrArgs &a, int nw)
+{
+    int n = 0;
+    for (int l = 0; l < a.L; ++l) {
+        const int x = net_bwd_parts(a.dims[l], a.dims[l + 1], nw) * kCtrBS * 64 * net_kblocks(a.dims[l]);
+        if (x > n) n = x;
+    }
+    return n;
+}
+
+// One net and the waves of the block that run it.
+struct NetRun {
+    float *act, *grd, *scr;
+    int w, nw, t, nt;                        // this wave of nw, this thread of nt
+};
+
+__device__ __forceinline__ NetRun net_run(const CtrArgs &a, float *base, float *scr, int w, int nw)
+{
+    NetRun n;
+    n.act = base;
+    n.grd = base + net_act_floats(a);
+    n.scr = scr;
+    n.w = w;
+    n.nw = nw;
+    n.t = w * AMS_WAVE + ams_lane();
+    n.nt = nw * AMS_WAVE;
+    return n;
+}
+
+// The field that column k of the concatenated input lies in, at k's place in
+// row i (out: the gradient's arrays; NULL where that field's is not wanted).
+__device__ __forceinline__ float *net_field(const CtrArgs &a, int k, int64_t i, bool out)
+{
+    float *p = nullptr;
+    int w = 0, at = 0, c0 = 0;
+#pragma unroll
+    for (int f = 0; f < kCtrMaxFields; ++f) {
+        if (f >= a.n_fields) break;
+        if (k >= c0) {
+            p = out ? a.dfield[f] : const_cast<float *>(a.field[f]);
+            w = a.fdim[f];
+            at = k - c0;
+        }
+        c0 += a.fdim[f];
+    }
+    return p ? p + i * w + at : nullptr;
+}
+
+// Input fields, concatenated (rows past B read 0), and the zero pad columns
+// of every layer.  A thread's loads are all in flight together.
+constexpr int kLoadBatch = 4;
+__device__ __forceinline__ void net_load(const CtrArgs &a, const NetRun &n, int b0, int B)
+{
+    const int K0 = a.dims[0], ld0 = net_ld(K0);
+    for (int e0 = n.t; e0 < kCtrBS * K0; e0 += kLoadBatch * n.nt) {
+        float v[kLoadBatch];
+#pragma unroll
+        for (int i = 0; i < kLoadBatch; ++i) {
+            const int e = e0 + i * n.nt, s = e / K0, k = e - s * K0;
+            const bool in = s < kCtrBS && b0 + s < B;
+            const float x = *net_field(a, in ? k : 0, in ? b0 + s : b0, false);
+            v[i] = in ? x : 0.f;
+        }
+#pragma unroll
+        for (int i = 0; i < kLoadBatch; ++i) {
+            const int e = e0 + i * n.nt, s = e / K0, k = e - s * K0;
+            if (s < kCtrBS) n.act[s * ld0 + k] = v[i];
+        }
+    }
+    int off = 0;
+    for (int l = 0; l <= a.L; ++l) {
+        const int w = a.dims[l], ld = net_ld(w), pad = ld - w;
+        for (int e = n.t; e < kCtrBS * pad; e += n.nt) {
+            const int x = off + (e / pad) * ld + w + e % pad;
+            n.act[x] = 0.f;
+            n.grd[x] = 0.f;
+        }
+        off += kCtrBS * ld;
+    }
 }
 
 // Activation of a hidden unit: ReLU, or PReLU with slope a (z for z > 0,
-// a z otherwise), whose pre-activation is kept in z_out for the backward.
-__device__ __forceinline__ float ctr_act(float v, const float *slope, int o, float *z_out)
+// a z otherwise).
+__device__ __forceinline__ float ctr_act(float v, const float *slope, float a) 
 {
-    if (!slope) return fmaxf(v, 0.f);
-    *z_out = v;
-    return v > 0.f ? v : slope[o] * v;
+    return v > 0.f ? v : slope ? a * v : 0.f;
 }
 
-// out[s][o] = bias[o] + sum_k in[s][k] W[o][k] for the block's kCtrBS
-// samples, activated below the last layer (`hidden`).  Work item (o, part p
-// of P): the K range of part p (a multiple of 4 wide), its W row streamed as
-// float4 (the next one loaded while the current one is used), all samples
-// accumulated together, k ascending (in[s][k..k+3] is one 16-byte LDS read,
-// the same address for the whole wave: a broadcast).  With P > 1 (narrow layers) the
-// parts go to `scr` [P][kCtrBS][O] and are added in part order.  With PReLU
-// the pre-activations go to zout [kCtrBS][O].
-__device__ __forceinline__ void ctr_dense_fwd(const float *in, int K, float *out, int O, const float *__restrict__ W,
-                                              const float *__restrict__ bias, bool hidden,
-                                              const float *__restrict__ slope, float *zout, float *scr, int t)
+// This lane's W operands of output tile ot of a layer, groups g0 .. g0 + 3:
+// row 16 ot + lane % 16 (rows past O read the last one, their results are
+// dropped), group g's quad k = 16 g + 4 (lane / 16) .. + 3 (zero past K).
+constexpr int kFwdBatch = 4;
+__device__ __forceinline__ void net_fwd_load(const float *__restrict__ W, int K, int O, int ot, int g0,
+                                             f4 (&w)[kFwdBatch])
 {
-    const int P = ctr_fwd_parts(K, O);
-    const int KC = (((K + P - 1) / P) + 3) & ~3;
-    for (int it = t; it < O * P; it += kCtrThreads) {
-        const int o = it % O, pp = it / O;
-        const int k0 = pp * KC, k1 = min(K, k0 + KC);
-        float acc[kCtrBS];
+    const int lane = ams_lane(), o = min(16 * ot + (lane & 15), O - 1), k0 = 16 * g0 + 4 * (lane >> 4);
+    const float *wr = W + (size_t)o * K;
+    if (16 * (g0 + kFwdBatch) <= K) {
 #pragma unroll
-        for (int s = 0; s < kCtrBS; ++s) acc[s] = 0.f;
-        const float *wr = W + (size_t)o * K;
-        if ((K & 3) == 0) {
-            // k0 and k1 are multiples of 4: 16 k per step in four groups of
-            // four, each sample's inputs of a group one 16-byte LDS read; the
-            // next step's 16 weights are loaded while this step computes
-            float4 wn[4];
+        for (int i = 0; i < kFwdBatch; ++i) w[i] = *(const f4u *)(wr + k0 + 16 * i);
+    } else if ((K & 3) == 0) {
 #pragma unroll
-            for (int q = 0; q < 4; ++q)
-                wn[q] = k0 + 4 * q < k1 ? *(const float4 *)(wr + k0 + 4 * q) : make_float4(0.f, 0.f, 0.f, 0.f);
-            for (int kb = k0; kb < k1; kb += 16) {
-                float4 wv[4];
-#pragma unroll
-                for (int q = 0; q < 4; ++q) wv[q] = wn[q];
-#pragma unroll
-                for (int q = 0; q < 4; ++q)
-                    if (kb + 16 + 4 * q < k1) wn[q] = *(const float4 *)(wr + kb + 16 + 4 * q);
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    if (kb + 4 * q < k1) {
-                        float4 x[kCtrBS];
-#pragma unroll
-                        for (int s = 0; s < kCtrBS; ++s) x[s] = *(const float4 *)(in + s * K + kb + 4 * q);
-#pragma unroll
-                        for (int s = 0; s < kCtrBS; ++s) {
-                            acc[s] = fmaf(x[s].x, wv[q].x, acc[s]);
-                            acc[s] = fmaf(x[s].y, wv[q].y, acc[s]);
-                            acc[s] = fmaf(x[s].z, wv[q].z, acc[s]);
-                            acc[s] = fmaf(x[s].w, wv[q].w, acc[s]);
-                        }
-                    }
-                }
-            }
-        } else {
-            for (int k = k0; k < k1; ++k) {
-                const float wk = wr[k];
-#pragma unroll
-                for (int s = 0; s < kCtrBS; ++s) acc[s] = fmaf(in[s * K + k], wk, acc[s]);
-            }
+        for (int i = 0; i < kFwdBatch; ++i) {
+            const bool in = k0 + 16 * i < K;
+            const f4 v = *(const f4u *)(wr + (in ? k0 + 16 * i : 0));
+            w[i] = in ? v : (f4){0.f, 0.f, 0.f, 0.f};
         }
-        if (P == 1) {
-            const float bo = bias[o];
-#pragma unroll
-            for (int s = 0; s < kCtrBS; ++s) {
-                const float v = acc[s] + bo;
-                out[s * O + o] = hidden ? ctr_act(v, slope, o, zout + s * O + o) : v;
-            }
-        } else {
-#pragma unroll
-            for (int s = 0; s < kCtrBS; ++s) scr[(pp * kCtrBS + s) * O + o] = acc[s];
-        }
-    }
-    if (P > 1) {
-        __syncthreads();
-        for (int e = t; e < kCtrBS * O; e += kCtrThreads) {
-            const int o = e % O;
-            float v = bias[o];
-            for (int pp = 0; pp < P; ++pp) v += scr[pp * kCtrBS * O + e];
-            out[e] = hidden ? ctr_act(v, slope, o, zout + e) : v;
-        }
-    }
-}
-
-// Gradient into a layer's input: d[s][k] = sum_o gout[s][o] W[o][k], then
-// through the activation that produced the input when `act` (below the
-// first layer): ReLU takes d where in > 0; PReLU reads its pre-activation z
-// from gin (left there by the forward) and takes d for z > 0, slope[k] d
-// otherwise, and adds d min(z, 0) over the block's samples (ascending) into
-// the slope gradient dsl[k].  Work item (k, part p of P over O, o ascending);
-// the lanes of a wave take consecutive k, so each W row read is contiguous
-// across the wave.  Parts are added in order through `scr` as in the
-// forward.
-__device__ __forceinline__ void ctr_act_bwd(float *gin, const float *in, int K, int k, const float (&d)[kCtrBS],
-                                            bool act, const float *__restrict__ slope, float *dsl)
-{
-    if (!act) {
-#pragma unroll
-        for (int s = 0; s < kCtrBS; ++s) gin[s * K + k] = d[s];
-    } else if (!slope) {
-#pragma unroll
-        for (int s = 0; s < kCtrBS; ++s) gin[s * K + k] = in[s * K + k] > 0.f ? d[s] : 0.f;
-        if (dsl) dsl[k] = 0.f;
     } else {
-        const float a = slope[k];
-        float ds = 0.f;
 #pragma unroll
-        for (int s = 0; s < kCtrBS; ++s) {
-            const float z = gin[s * K + k];
-            const bool pos = z > 0.f;
-            gin[s * K + k] = pos ? d[s] : a * d[s];
-            ds = fmaf(pos ? 0.f : z, d[s], ds);
-        }
-        dsl[k] = ds;
+        for (int i = 0; i < kFwdBatch; ++i)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int k = k0 + 16 * i + e;
+                const float v = wr[min(k, K - 1)];
+                w[i][e] = k < K ? v : 0.f;
+            }
     }
 }
 
-__device__ __forceinline__ void ctr_dense_bwd_data(const float *gout, int O, float *gin, const float *in, int K,
-                                                   const float *__restrict__ W, bool act,
-                                                   const float *__restrict__ slope, float *dsl, float *scr, int t)
+// out[s][o] = act(b[o] + sum_k in[s][k] W[o][k]): output tile ot (w: its
+// first operands, afterwards those of tile next); the result's rows are outputs, so a lane holds four
+// consecutive outputs of one sample.  With PReLU the pre-activations go to
+// zout.
+__device__ __forceinline__ void net_fwd_tile(const float *in, int ldi, int K, float *out, float *zout, int ldo, int O,
+                                             int ot, int next, f4 (&w)[kFwdBatch], const float *__restrict__ W,
+                                             const float *__restrict__ bias, bool hidden,
+                                             const float *__restrict__ slope)
 {
-    const int P = ctr_bwd_parts(K, O);
-    const int OC = (((O + P - 1) / P) + 3) & ~3;
-    for (int it = t; it < K * P; it += kCtrThreads) {
-        const int k = it % K, pp = it / K;
-        const int o0 = pp * OC, o1 = min(O, o0 + OC);
-        float acc[kCtrBS];
+    const int lane = ams_lane(), s = lane & 15, q = lane >> 4, o0 = 16 * ot + 4 * q, groups = (K + 15) / 16;
+    float b[4], sl[4];
 #pragma unroll
-        for (int s = 0; s < kCtrBS; ++s) acc[s] = 0.f;
-        if ((O & 3) == 0) {
-            // 16 o per step in groups of four: the samples' gradients of a
-            // group as 16-byte LDS reads; the next step's 16 W values are
-            // loaded while this step computes
-            float wn[16];
-#pragma unroll
-            for (int q = 0; q < 16; ++q) wn[q] = o0 + q < o1 ? W[(size_t)(o0 + q) * K + k] : 0.f;
-            for (int ob = o0; ob < o1; ob += 16) {
-                float w[16];
-#pragma unroll
-                for (int q = 0; q < 16; ++q) w[q] = wn[q];
-#pragma unroll
-                for (int q = 0; q < 16; ++q)
-                    if (ob + 16 + q < o1) wn[q] = W[(size_t)(ob + 16 + q) * K + k];
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    if (ob + 4 * q < o1) {
-                        float4 g[kCtrBS];
-#pragma unroll
-                        for (int s = 0; s < kCtrBS; ++s) g[s] = *(const float4 *)(gout + s * O + ob + 4 * q);
-#pragma unroll
-                        for (int s = 0; s < kCtrBS; ++s) {
-                            acc[s] = fmaf(g[s].x, w[4 * q], acc[s]);
-                            acc[s] = fmaf(g[s].y, w[4 * q + 1], acc[s]);
-                            acc[s] = fmaf(g[s].z, w[4 * q + 2], acc[s]);
-                            acc[s] = fmaf(g[s].w, w[4 * q + 3], acc[s]);
-                        }
-                    }
-                }
-            }
-        } else {
-            for (int o = o0; o < o1; ++o) {
-                const float wo = W[(size_t)o * K + k];
-#pragma unroll
-                for (int s = 0; s < kCtrBS; ++s) acc[s] = fmaf(gout[s * O + o], wo, acc[s]);
-            }
-        }
-        if (P == 1) {
-            ctr_act_bwd(gin, in, K, k, acc, act, slope, dsl);
-        } else {
-#pragma unroll
-            for (int s = 0; s < kCtrBS; ++s) scr[(pp * kCtrBS + s) * K + k] = acc[s];
-        }
+    for (int e = 0; e < 4; ++e) {
+        b[e] = bias[min(o0 + e, O - 1)];
+        sl[e] = slope ? slope[min(o0 + e, O - 1)] : 0.f;
     }
-    if (P > 1) {
-        __syncthreads();
-        for (int k = t; k < K; k += kCtrThreads) {
-            float d[kCtrBS];
+    // four chains, added at the end: no MFMA waits for the one before it, and
+    // a sum's rounding grows with a quarter of its terms
+    f4 acc[4];
 #pragma unroll
-            for (int s = 0; s < kCtrBS; ++s) {
-                float v = 0.f;
-                for (int pp = 0; pp < P; ++pp) v += scr[(pp * kCtrBS + s) * K + k];
-                d[s] = v;
-            }
-            ctr_act_bwd(gin, in, K, k, d, act, slope, dsl);
+    for (int e = 0; e < 4; ++e) acc[e] = (f4){0.f, 0.f, 0.f, 0.f};
+    const float *x0 = in + s * ldi;
+#pragma unroll 1
+    for (int g = 0; g < groups; g += kFwdBatch) {
+        f4 nx[kFwdBatch];
+        if (g + kFwdBatch < groups) net_fwd_load(W, K, O, ot, g + kFwdBatch, nx);
+        else if (16 * next < O) net_fwd_load(W, K, O, next, 0, nx);
+        f4 x[kFwdBatch];
+#pragma unroll
+        for (int i = 0; i < kFwdBatch; ++i) x[i] = net_quad(x0, 16 * (g + i) + 4 * q, K);
+#pragma unroll
+        for (int i = 0; i < kFwdBatch; ++i) {
+            if (g + i >= groups) break;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[e] = mfma4(w[i][e], x[i][e], acc[e]);
         }
+#pragma unroll
+        for (int i = 0; i < kFwdBatch; ++i) w[i] = nx[i];
+    }
+    f4 z, y;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        z[e] = o0 + e < O ? ((acc[0][e] + acc[1][e]) + (acc[2][e] + acc[3][e])) + b[e] : 0.f;
+        y[e] = hidden ? ctr_act(z[e], slope, sl[e]) : z[e];
+    }
+    if (o0 < O) {
+        *(f4 *)(out + s * ldo + o0) = y;
+        if (hidden && slope) *(f4 *)(zout + s * ldo + o0) = z;
     }
 }
 
-// Partial dW[o][k] = sum_s gout[s][o] in[s][k] over the block's samples and
-// db[o] = sum_s gout[s][o], in 4 x 4 register tiles (8 LDS words per sample
-// feed 16 FMAs); written to the block's partial row at p (dW, then db).
-__device__ __forceinline__ void ctr_dense_bwd_weight(const float *gout, int O, const float *in, int K,
-                                                     float *__restrict__ p, int t)
+// Layer l of the forward (w holds the first operands of this wave's first
+// tile, and afterwards those of the next layer's).
+__device__ __forceinline__ void net_fwd_layer(const CtrArgs &a, const NetRun &n, int l, f4 (&w)[kFwdBatch])
 {
-    const int to = (O + 3) / 4, tk = (K + 3) / 4;
-    const bool v4 = ((O | K) & 3) == 0;
-    for (int it = t; it < to * tk; it += kCtrThreads) {
-        const int o0 = 4 * (it / tk), k0 = 4 * (it % tk);
-        float acc[4][4];
+    const int K = a.dims[l], O = a.dims[l + 1], tiles = (O + 15) / 16;
+    const int oi = net_off(a, l), oo = oi + kCtrBS * net_ld(K);
+    const bool hidden = l < a.L - 1;
+#pragma unroll 1
+    for (int ot = n.w; ot < tiles; ot += n.nw) {
+        net_fwd_tile(n.act + oi, net_ld(K), K, n.act + oo, n.grd + oo, net_ld(O), O, ot, ot + n.nw, w, a.W[l], a.b[l],
+                     hidden, hidden ? a.slope[l] : nullptr);
+    }
+    if (hidden && 16 * n.w < a.dims[l + 2]) net_fwd_load(a.W[l + 1], O, a.dims[l + 2], n.w, 0, w);
+}
+
+// dW[o][k] = sum_s gout[s][o] in[s][k] over the block's samples: 16 outputs x
+// 64 inputs per wave and turn, written to the partial row at p; then
+// db[o] = sum_s gout[s][o].
+__device__ __forceinline__ void net_bwd_weight(const float *gout, int ldg, int O, const float *in, int ldi, int K,
+                                               float *__restrict__ p, const NetRun &n)
+{
+    const int lane = ams_lane(), c = lane & 15, q = lane >> 4;
+    const int kbs = net_kblocks(K), jobs = ((O + 15) / 16) * kbs;
+#pragma unroll 1
+    for (int j = n.w; j < jobs; j += n.nw) {
+        const int ot = j / kbs, k = 64 * (j % kbs) + 4 * c;
+        const float *gp = gout + 4 * q * ldg + 16 * ot + c, *xp = in + 4 * q * ldi + min(k, ldi - 4);
+        f4 acc[4];
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+        for (int e = 0; e < 4; ++e) acc[e] = (f4){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int j = 0; j < 4; ++j) acc[i][j] = 0.f;
-        if (v4) {
-            // two 16-byte LDS reads per sample feed 16 FMAs
-#pragma unroll 4
-            for (int s = 0; s < kCtrBS; ++s) {
-                const float4 g = *(const float4 *)(gout + s * O + o0);
-                const float4 x = *(const float4 *)(in + s * K + k0);
-                const float gv[4] = {g.x, g.y, g.z, g.w}, xv[4] = {x.x, x.y, x.z, x.w};
+        for (int st = 0; st < 4; ++st) {                  // samples 4 q + st
+            const float g = gp[st * ldg];
+            const f4 x = *(const f4 *)(xp + st * ldi);
 #pragma unroll
-                for (int i = 0; i < 4; ++i)
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(gv[i], xv[j], acc[i][j]);
-            }
-        } else {
-#pragma unroll 4
-            for (int s = 0; s < kCtrBS; ++s) {
-                float g[4], x[4];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) g[i] = o0 + i < O ? gout[s * O + o0 + i] : 0.f;
-#pragma unroll
-                for (int j = 0; j < 4; ++j) x[j] = k0 + j < K ? in[s * K + k0 + j] : 0.f;
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(g[i], x[j], acc[i][j]);
-            }
+            for (int e = 0; e < 4; ++e) acc[e] = mfma4(g, x[e], acc[e]);
         }
-        if (v4) {
-            // a row of the tile is 16 contiguous bytes; across the lanes of a
-            // wave (consecutive k0) the stores are contiguous
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
-                *(float4 *)(p + (o0 + i) * K + k0) = make_float4(acc[i][0], acc[i][1], acc[i][2], acc[i][3]);
-        } else {
+        for (int r = 0; r < 4; ++r) {
+            const int o = 16 * ot + 4 * q + r;
+            if (o >= O) continue;
+            float *dst = p + o * K + k;
+            if (k + 3 < K) *(f4u *)dst = (f4){acc[0][r], acc[1][r], acc[2][r], acc[3][r]};
+            else
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    if (o0 + i < O && k0 + j < K) p[(o0 + i) * K + k0 + j] = acc[i][j];
+                for (int e = 0; e < 4; ++e)
+                    if (k + e < K) dst[e] = acc[e][r];
         }
     }
-    for (int o = t; o < O; o += kCtrThreads) {
+    for (int o = n.t; o < O; o += n.nt) {
         float acc = 0.f;
 #pragma unroll
-        for (int s = 0; s < kCtrBS; ++s) acc += gout[s * O + o];
+        for (int s = 0; s < kCtrBS; ++s) acc += gout[s * ldg + o];
         p[O * K + o] = acc;
     }
 }
 
-// LDS of one net for a block of kCtrBS samples: act (every layer's
-// activations, [kCtrBS][dims[l]] each, the input fields first) and grd (the
-// loss gradient of each act[l]; with PReLU a hidden layer's slot holds its
-// pre-activations between the forward and the backward).
-__host__ __device__ inline int ctr_act_floats(const CtrArgs &a)
+// This lane's W operands of the data gradient's groups g0, g0 + 1 (outputs
+// 16 g + 4 (lane / 16) + e, zero past O) for the inputs k .. k + 3.
+constexpr int kBwdBatch = 2;
+__device__ __forceinline__ void net_bwd_load(const float *__restrict__ W, int K, int O, int k, int g0, int g1,
+                                             f4 (&w)[kBwdBatch][4])
 {
-    int n = 0;
-    for (int l = 0; l <= a.L; ++l) n += kCtrBS * a.dims[l];
-    return n;
-}
-
-// scr: the parts of narrow layers, forward and backward.
-__host__ __device__ inline int ctr_scr_floats(const CtrArgs &a)
-{
-    int n = 0;
-    for (int l = 0; l < a.L; ++l) {
-        const int K = a.dims[l], O = a.dims[l + 1];
-        const int pf = ctr_fwd_parts(K, O), pb = ctr_bwd_parts(K, O);
-        if (pf > 1 && pf * kCtrBS * O > n) n = pf * kCtrBS * O;
-        if (pb > 1 && pb * kCtrBS * K > n) n = pb * kCtrBS * K;
-    }
-    return n;
-}
-
-struct NetLds {
-    float *act, *grd;
-    int off[kCtrMaxLayers + 1];
-};
-
-__device__ __forceinline__ NetLds net_lds(const CtrArgs &a, float *base)
-{
-    NetLds n;
-    n.act = base;
-    n.grd = base + ctr_act_floats(a);
-    n.off[0] = 0;
-    for (int l = 0; l < a.L; ++l) n.off[l + 1] = n.off[l] + kCtrBS * a.dims[l];
-    return n;
-}
-
-// input fields, concatenated; rows past B read 0
-__device__ __forceinline__ void net_load(const CtrArgs &a, const NetLds &n, int b0, int B, int t)
-{
-    const int K0 = a.dims[0];
-    int c0 = 0;
-    for (int f = 0; f < a.n_fields; ++f) {
-        const int w = a.fdim[f];
-        for (int e = t; e < kCtrBS * w; e += kCtrThreads) {
-            const int s = e / w, k = e % w;
-            n.act[s * K0 + c0 + k] = (b0 + s < B) ? a.field[f][(size_t)(b0 + s) * w + k] : 0.f;
+    // inputs past K: any address of the row, their columns are dropped
+    const int q = ams_lane() >> 4;
+    const bool vec = (K & 3) == 0 || (k | 63) < K;         // (the same for the whole wave)
+#pragma unroll
+    for (int i = 0; i < kBwdBatch; ++i) {
+        if (g0 + i >= g1) break;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const float *wr = W + (size_t)min(16 * (g0 + i) + 4 * q + e, O - 1) * K;
+            if (vec) w[i][e] = *(const f4u *)(wr + (k < K ? k : 0));
+            else
+#pragma unroll
+                for (int c = 0; c < 4; ++c) w[i][e][c] = wr[min(k + c, K - 1)];
         }
-        c0 += w;
+        if (16 * (g0 + i) + 16 > O)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (16 * (g0 + i) + 4 * q + e >= O) w[i][e] = (f4){0.f, 0.f, 0.f, 0.f};
     }
 }
 
-// Every layer in turn (the caller synchronises before: act[0] loaded).
-__device__ __forceinline__ void net_forward(const CtrArgs &a, const NetLds &n, float *scr, int t)
+// The layer's data gradient, through the activation that produced its input
+// (act, below the first layer): d[s][k] = sum_o gout[s][o] W[o][k] in parts
+// over O, added in part order; ReLU takes d where in > 0; PReLU reads its
+// pre-activation z from gin (left there by the forward) and takes d for
+// z > 0, slope[k] d otherwise, and adds d min(z, 0) over the block's samples
+// (ascending) into the slope gradient dsl[k].
+__device__ __forceinline__ void net_bwd_parts_out(const float *__restrict__ W, int K, int O, const float *gout, int ldg,
+                                                  const NetRun &n, f4 (&w)[kBwdBatch][4])
 {
-    for (int l = 0; l < a.L; ++l) {
-        const bool hidden = l < a.L - 1;
-        ctr_dense_fwd(n.act + n.off[l], a.dims[l], n.act + n.off[l + 1], a.dims[l + 1], a.W[l], a.b[l], hidden,
-                      hidden ? a.slope[l] : nullptr, n.grd + n.off[l + 1], scr, t);
-        __syncthreads();
-    }
-}
-
-// From the loss gradient of the last layer's output (in grd, synchronised):
-// each layer's weight, bias and slope gradients over the block's samples into
-// the partial row p, and the gradient of the input fields into grd[0].
-__device__ __forceinline__ void net_backward(const CtrArgs &a, const NetLds &n, float *scr, float *p, int t)
-{
-    int wo[kCtrMaxLayers];
-    int woff = 0;
-    for (int l = 0; l < a.L; ++l) {
-        wo[l] = woff;
-        woff += net_layer_size(a, l);
-    }
-    for (int l = a.L - 1; l >= 0; --l) {
-        const int K = a.dims[l], O = a.dims[l + 1];
-        const float *gout = n.grd + n.off[l + 1], *in = n.act + n.off[l];
-        ctr_dense_bwd_weight(gout, O, in, K, p + wo[l], t);
-        // the activation below layer l belongs to layer l - 1: its slot
-        // follows that layer's dW and db
-        float *dsl = l > 0 ? p + wo[l - 1] + K * a.dims[l - 1] + K : nullptr;
-        ctr_dense_bwd_data(gout, O, n.grd + n.off[l], in, K, a.W[l], l > 0, l > 0 ? a.slope[l - 1] : nullptr, dsl,
-                           scr, t);
-        __syncthreads();
-    }
-}
-
-__device__ __forceinline__ void net_store_dfields(const CtrArgs &a, const NetLds &n, int b0, int B, int t)
-{
-    const int K0 = a.dims[0];
-    int c0 = 0;
-    for (int f = 0; f < a.n_fields; ++f) {
-        const int w = a.fdim[f];
-        if (a.dfield[f])
-            for (int e = t; e < kCtrBS * w; e += kCtrThreads) {
-                const int s = e / w, k = e % w;
-                if (b0 + s < B) a.dfield[f][(size_t)(b0 + s) * w + k] = n.grd[s * K0 + c0 + k];
+    const int lane = ams_lane(), c = lane & 15, q = lane >> 4;
+    const int kbs = net_kblocks(K), P = net_bwd_parts(K, O, n.nw), groups = (O + 15) / 16;
+#pragma unroll 1
+    for (int j = n.w; j < kbs * P; j += n.nw) {
+        const int kb = j % kbs, pp = j / kbs, k = 64 * kb + 4 * c;
+        const int g0 = pp * groups / P, g1 = (pp + 1) * groups / P;
+        f4 acc[2][4];                                      // even and odd e: two chains
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[0][e] = acc[1][e] = (f4){0.f, 0.f, 0.f, 0.f};
+        if (j != n.w) net_bwd_load(W, K, O, k, g0, g1, w);
+#pragma unroll 1
+        for (int g = g0; g < g1; g += kBwdBatch) {
+            f4 nx[kBwdBatch][4];
+            if (g + kBwdBatch < g1) net_bwd_load(W, K, O, k, g + kBwdBatch, g1, nx);
+            f4 x[kBwdBatch];
+#pragma unroll
+            for (int i = 0; i < kBwdBatch; ++i) x[i] = net_quad(gout + c * ldg, 16 * (g + i) + 4 * q, O);
+#pragma unroll
+            for (int i = 0; i < kBwdBatch; ++i) {
+                if (g + i >= g1) break;
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+#pragma unroll
+                    for (int e2 = 0; e2 < 4; ++e2) acc[e & 1][e2] = mfma4(x[i][e], w[i][e][e2], acc[e & 1][e2]);
             }
-        c0 += w;
+#pragma unroll
+            for (int i = 0; i < kBwdBatch; ++i)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) w[i][e] = nx[i][e];
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[0][e] += acc[1][e];
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            *(f4 *)(n.scr + (pp * kCtrBS + 4 * q + r) * 64 * kbs + k) =
+                (f4){acc[0][0][r], acc[0][1][r], acc[0][2][r], acc[0][3][r]};
     }
 }
 
+// The sum of the parts: TS threads (adjacent lanes) per input k, each with
+// 16 / TS of the samples.
+template <int TS>
+__device__ __forceinline__ void net_bwd_combine(float *gin, const float *in, int ldi, int K, int O, bool act,
+                                                const float *__restrict__ slope, float *dsl, const NetRun &n)
+{
+    constexpr int NS = kCtrBS / TS;
+    const int lds = 64 * net_kblocks(K), P = net_bwd_parts(K, O, n.nw), s0 = (n.t % TS) * NS;
+    for (int k = n.t / TS; k < K; k += n.nt / TS) {
+        const float a = slope ? slope[k] : 0.f;
+        float d[NS];
+#pragma unroll
+        for (int s = 0; s < NS; ++s) d[s] = 0.f;
+        for (int pp = 0; pp < P; ++pp)
+#pragma unroll
+            for (int s = 0; s < NS; ++s) d[s] += n.scr[(pp * kCtrBS + s0 + s) * lds + k];
+        float ds = 0.f;
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+            const int x = (s0 + s) * ldi + k;
+            if (act) {
+                const float z = slope ? gin[x] : in[x];
+                const bool pos = z > 0.f;
+                ds = fmaf(pos ? 0.f : z, d[s], ds);
+                d[s] = pos ? d[s] : slope ? a * d[s] : 0.f;
+            }
+            gin[x] = d[s];
+        }
+        if (act) {
+#pragma unroll
+            for (int o = 1; o < TS; o <<= 1) ds += __shfl_xor(ds, o, AMS_WAVE);
+            if (n.t % TS == 0) dsl[k] = slope ? ds : 0.f;
+        }
+    }
+}
+
+// The data gradients run down the layers first, two halves per layer with a
+// barrier after each (the parts, then their sum); the weight gradients, whose
+// stores a later load's wait would have to sit out, come after all of them
+// (every layer's activations and gradients stay in LDS).
+__device__ __forceinline__ void net_bwd_preload(const CtrArgs &a, const NetRun &n, int l, f4 (&w)[kBwdBatch][4])
+{
+    const int K = a.dims[l], O = a.dims[l + 1], kbs = net_kblocks(K), P = net_bwd_parts(K, O, n.nw);
+    if (n.w < kbs * P) {
+        const int pp = n.w / kbs, groups = (O + 15) / 16;
+        net_bwd_load(a.W[l], K, O, 64 * (n.w % kbs) + 4 * (ams_lane() & 15), pp * groups / P, (pp + 1) * groups / P, w);
+    }
+}
+
+__device__ __forceinline__ void net_bwd_first(const CtrArgs &a, const NetRun &n, int l, f4 (&w)[kBwdBatch][4])
+{
+    const int K = a.dims[l], O = a.dims[l + 1];
+    net_bwd_parts_out(a.W[l], K, O, n.grd + net_off(a, l + 1), net_ld(O), n, w);
+    if (l > 0) net_bwd_preload(a, n, l - 1, w);
+}
+
+__device__ __forceinline__ void net_bwd_weights(const CtrArgs &a, const NetRun &n, float *p)
+{
+#pragma unroll 1
+    for (int l = 0; l < a.L; ++l) {
+        const int K = a.dims[l], O = a.dims[l + 1], oi = net_off(a, l);
+        net_bwd_weight(n.grd + oi + kCtrBS * net_ld(K), net_ld(O), O, n.act + oi, net_ld(K), K, p, n);
+        p += net_layer_size(a, l);
+    }
+}
+
+__device__ __forceinline__ void net_bwd_second(const CtrArgs &a, const NetRun &n, int l, float *p)
+{
+    const int K = a.dims[l];
+    // the activation below layer l belongs to layer l - 1: its slot follows
+    // that layer's dW and db
+    float *dsl = p;
+    if (l > 0) {
+        for (int x = 0; x < l - 1; ++x) dsl += net_layer_size(a, x);
+        dsl += K * a.dims[l - 1] + K;
+    }
+    const int oi = net_off(a, l);
+    const float *slope = l > 0 ? a.slope[l - 1] : nullptr;
+    if (4 * K <= n.nt) net_bwd_combine<4>(n.grd + oi, n.act + oi, net_ld(K), K, a.dims[l + 1], l > 0, slope, dsl, n);
+    else net_bwd_combine<2>(n.grd + oi, n.act + oi, net_ld(K), K, a.dims[l + 1], l > 0, slope, dsl, n);
+}
+
+__device__ __forceinline__ void net_store_dfields(const CtrArgs &a, const NetRun &n, int b0, int B)
+{
+    const int K0 = a.dims[0], ld0 = net_ld(K0);
+    for (int e = n.t; e < kCtrBS * K0; e += n.nt) {
+        const int s = e / K0, k = e - s * K0;
+        if (b0 + s >= B) continue;
+        float *p = net_field(a, k, b0 + s, true);
+        if (p) *p = n.grd[s * ld0 + k];
+    }
+}
+
+constexpr int kCtrWaves = kCtrThreads / AMS_WAVE;
+
+// LDS of a block: per net act and grd, then the samples' losses and the parts
+// of the data gradients.
 inline size_t ctr_lds_bytes(const CtrArgs &a)
 {
-    return (size_t)(2 * ctr_act_floats(a) + ctr_scr_floats(a) + kCtrBS) * 4;
+    return (size_t)(2 * net_act_floats(a) + kCtrBS + net_scr_floats(a, kCtrWaves)) * 4;
+}
+
+// Which widths the calls take: the sum of the nets' activations, twice, and of
+// the parts of a 512-thread block's widest layer has to fit the LDS (a bound
+// the kernels' own need never passes).
+inline size_t net_width_bytes(const CtrArgs *const *nets, int count)
+{
+    int act = 0, parts = 0;
+    for (int i = 0; i < count; ++i) {
+        const CtrArgs &a = *nets[i];
+        for (int l = 0; l <= a.L; ++l) act += kCtrBS * a.dims[l];
+        for (int l = 0; l < a.L; ++l) {
+            const int K = a.dims[l], O = a.dims[l + 1];
+            const int pf = min(max(kCtrThreads / O, 1), (K + 15) / 16), pb = min(max(kCtrThreads / K, 1), (O + 7) / 8);
+            if (pf > 1) parts = max(parts, pf * kCtrBS * O);
+            if (pb > 1) parts = max(parts, pb * kCtrBS * K);
+        }
+    }
+    return (size_t)(2 * act + parts + kCtrBS) * 4;
+}
+
+// The towers run side by side, each with its own parts; where that does not
+// fit the LDS (tight), their backwards take turns with one area for both,
+// which every pair of widths that the call takes fits.
+inline size_t dssm_lds_bytes(const CtrArgs &u, const CtrArgs &v, bool tight)
+{
+    const int su = net_scr_floats(u, kCtrWaves / 2), sv = net_scr_floats(v, kCtrWaves / 2);
+    return (size_t)(2 * (net_act_floats(u) + net_act_floats(v)) + kCtrBS + (tight ? max(su, sv) : su + sv)) * 4;
 }
 
 // One block = kCtrBS samples: forward through every layer in LDS, softmax
@@ -532,23 +664,33 @@ inline size_t ctr_lds_bytes(const CtrArgs &a)
 __global__ __launch_bounds__(kCtrThreads) void ctr_fb_k(CtrArgs a, int B, const int32_t *__restrict__ labels,
                                                      float *__restrict__ prob, float *__restrict__ part, int PS)
 {
-    extern __shared__ float lds[];
-    const NetLds n = net_lds(a, lds);
-    float *scr = lds + 2 * ctr_act_floats(a);
-    float *lossv = scr + ctr_scr_floats(a);
+    extern __shared__ __attribute__((aligned(16))) float lds[];
+    net_args_touch<sizeof(CtrArgs) / 64 + 1>();
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / AMS_WAVE);
+    float *lossv = lds + 2 * net_act_floats(a);
+    const NetRun n = net_run(a, lds, lossv + kCtrBS, wave, kCtrWaves);
     const int t = threadIdx.x;
     const int b0 = blockIdx.x * kCtrBS;
     const int L = a.L, C = a.dims[L];
-    net_load(a, n, b0, B, t);
-    __syncthreads();
-    net_forward(a, n, scr, t);
+    f4 w[kFwdBatch];
+    if (16 * wave < a.dims[1]) net_fwd_load(a.W[0], a.dims[0], a.dims[1], wave, 0, w);
+    const int y = t < kCtrBS && b0 + t < B ? labels[b0 + t] : -1;
+    net_load(a, n, b0, B);
+    lds_barrier();
+#pragma unroll 1
+    for (int l = 0; l < L; ++l) {
+        net_fwd_layer(a, n, l, w);
+        lds_barrier();
+    }
+    f4 wb[kBwdBatch][4];
+    net_bwd_preload(a, n, L - 1, wb);
     // softmax, cross-entropy, dlogits = (p - onehot(y)) / B
     if (t < kCtrBS) {
         const int s = t, i = b0 + s;
-        const float *z = n.act + n.off[L] + s * C;
-        float *gz = n.grd + n.off[L] + s * C;
+        const int oz = net_off(a, L) + s * net_ld(C);
+        const float *z = n.act + oz;
+        float *gz = n.grd + oz;
         float ls = 0.f;
-        const int y = i < B ? labels[i] : -1;
         if (i < B && y >= 0 && y < C) {
             float m = z[0];
             for (int c = 1; c < C; ++c) m = fmaxf(m, z[c]);
@@ -568,10 +710,17 @@ __global__ __launch_bounds__(kCtrThreads) void ctr_fb_k(CtrArgs a, int B, const 
         }
         lossv[s] = ls;
     }
-    __syncthreads();
+    lds_barrier();
     float *p = part + (size_t)blockIdx.x * PS;
-    net_backward(a, n, scr, p, t);
-    net_store_dfields(a, n, b0, B, t);
+#pragma unroll 1
+    for (int l = L - 1; l >= 0; --l) {
+        net_bwd_first(a, n, l, wb);
+        lds_barrier();
+        net_bwd_second(a, n, l, p);
+        lds_barrier();
+    }
+    net_store_dfields(a, n, b0, B);
+    net_bwd_weights(a, n, p);
     if (t == 0) {
         float ls = 0.f;
         for (int s = 0; s < kCtrBS; ++s) ls += lossv[s];
@@ -583,31 +732,46 @@ __global__ __launch_bounds__(kCtrThreads) void ctr_fb_k(CtrArgs a, int B, const 
 // fields, score s = <u, a> of their outputs, click probability sigmoid(s),
 // logistic loss softplus(s) - y s for y in {0, 1} (other labels add
 // nothing), divided by B.  Same block layout as the CTR kernel with both
-// towers in LDS; the partial row holds the user tower's gradients, then the
-// ad tower's, then the loss sum.
-__global__ __launch_bounds__(kCtrThreads) void dssm_fb_k(CtrArgs u, CtrArgs v, int B, const int32_t *__restrict__ labels,
+// towers in LDS, four waves each side by side; the partial row holds the user
+// tower's gradients, then the ad tower's, then the loss sum.
+struct TowerArgs {
+    CtrArgs n[2];                            // user, ad
+};
+
+__global__ __launch_bounds__(kCtrThreads) void dssm_fb_k(TowerArgs a2, int tight, int B, const int32_t *__restrict__ labels,
                                                       float *__restrict__ prob, float *__restrict__ part, int PS)
 {
-    extern __shared__ float lds[];
-    const NetLds nu = net_lds(u, lds);
-    const NetLds nv = net_lds(v, lds + 2 * ctr_act_floats(u));
-    float *scr = lds + 2 * ctr_act_floats(u) + 2 * ctr_act_floats(v);
-    float *lossv = scr + max(ctr_scr_floats(u), ctr_scr_floats(v));
+    extern __shared__ __attribute__((aligned(16))) float lds[];
+    constexpr int half = kCtrWaves / 2;
+    net_args_touch<sizeof(TowerArgs) / 64 + 1>();
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / AMS_WAVE);
+    const int ad = wave / half;
+    const CtrArgs &a = a2.n[ad], &u = a2.n[0], &v = a2.n[1];
+    const int fu = 2 * net_act_floats(u);
+    float *lossv = lds + fu + 2 * net_act_floats(v), *scr = lossv + kCtrBS;
+    const NetRun n = net_run(a, lds + (ad ? fu : 0), scr + (ad && !tight ? net_scr_floats(u, half) : 0), wave % half, half);
     const int t = threadIdx.x;
     const int b0 = blockIdx.x * kCtrBS;
-    const int R = u.dims[u.L];
-    net_load(u, nu, b0, B, t);
-    net_load(v, nv, b0, B, t);
-    __syncthreads();
-    net_forward(u, nu, scr, t);
-    net_forward(v, nv, scr, t);
+    const int R = u.dims[u.L], Lmax = max(u.L, v.L);
+    f4 w[kFwdBatch];
+    if (16 * n.w < a.dims[1]) net_fwd_load(a.W[0], a.dims[0], a.dims[1], n.w, 0, w);
+    const int y = t < kCtrBS && b0 + t < B ? labels[b0 + t] : -1;
+    net_load(a, n, b0, B);
+    lds_barrier();
+#pragma unroll 1
+    for (int l = 0; l < Lmax; ++l) {
+        if (l < a.L) net_fwd_layer(a, n, l, w);
+        lds_barrier();
+    }
+    f4 wb[kBwdBatch][4];
+    net_bwd_preload(a, n, a.L - 1, wb);
     if (t < kCtrBS) {
         const int s = t, i = b0 + s;
-        const float *zu = nu.act + nu.off[u.L] + s * R, *zv = nv.act + nv.off[v.L] + s * R;
+        const int ld = net_ld(R), ou = net_off(u, u.L) + s * ld, ov = fu + net_off(v, v.L) + s * ld;
+        const float *zu = lds + ou, *zv = lds + ov;
         float sc = 0.f;
         for (int r = 0; r < R; ++r) sc = fmaf(zu[r], zv[r], sc);
         const float pr = 1.f / (1.f + expf(-sc));
-        const int y = i < B ? labels[i] : -1;
         float ls = 0.f, g = 0.f;
         if (i < B) {
             if (prob) prob[i] = pr;
@@ -616,19 +780,27 @@ __global__ __launch_bounds__(kCtrThreads) void dssm_fb_k(CtrArgs u, CtrArgs v, i
                 g = (pr - (float)y) / (float)B;
             }
         }
-        float *gu = nu.grd + nu.off[u.L] + s * R, *gv = nv.grd + nv.off[v.L] + s * R;
+        float *gu = lds + net_act_floats(u) + ou, *gv = lds + net_act_floats(v) + ov;
         for (int r = 0; r < R; ++r) {
             gu[r] = g * zv[r];
             gv[r] = g * zu[r];
         }
         lossv[s] = ls;
     }
-    __syncthreads();
+    lds_barrier();
     float *p = part + (size_t)blockIdx.x * PS;
-    net_backward(u, nu, scr, p, t);
-    net_backward(v, nv, scr, p + net_part_size(u), t);
-    net_store_dfields(u, nu, b0, B, t);
-    net_store_dfields(v, nv, b0, B, t);
+    float *pn = p + (ad ? net_part_size(u) : 0);
+#pragma unroll 1
+    for (int i = 0; i < (tight ? 2 : 1) * Lmax; ++i) {
+        const int l = a.L - 1 - i % Lmax;
+        const bool mine = l >= 0 && (!tight || i / Lmax == ad);
+        if (mine) net_bwd_first(a, n, l, wb);
+        lds_barrier();
+        if (mine) net_bwd_second(a, n, l, pn);
+        lds_barrier();
+    }
+    net_store_dfields(a, n, b0, B);
+    net_bwd_weights(a, n, pn);
     if (t == 0) {
         float ls = 0.f;
         for (int s = 0; s < kCtrBS; ++s) ls += lossv[s];
@@ -652,17 +824,20 @@ struct CtrOut {
 };
 
 // Fixed-order sum of the blocks' partial rows, scattered into the gradients
-// and the mean loss.  A block takes 64 elements; wave q of its 4 sums the
-// q-th quarter of the G rows (eight running chains over g = 8 i + r, added
-// r = 0..7), and the quarters are added in order.
-constexpr int kRedCols = kThreads / 4;
+// and the mean loss.  A block takes 64 elements; each of its 16 waves sums a
+// sixteenth of the G rows (eight running chains over g = 8 i + r, added
+// r = 0..7), and the sixteenths are added in order.  4096 samples of the
+// 72-200-80-2 net (31 MB of partial rows): with four waves per 64 elements
+// 8.5 us, 8.1 us so; the towers' 9 k elements 6.4 and 5.0 us (more loads in
+// flight).
+constexpr int kRedCols = AMS_WAVE, kRedWaves = 16, kRedThreads = kRedWaves * AMS_WAVE;
 
-__global__ __launch_bounds__(kThreads) void ctr_reduce_k(const float *__restrict__ part, int G, int PS, CtrOut o)
+__global__ __launch_bounds__(kRedThreads) void ctr_reduce_k(const float *__restrict__ part, int G, int PS, CtrOut o)
 {
-    __shared__ float q4[4][kRedCols];
+    __shared__ float q16[kRedWaves][kRedCols];
     const int c = threadIdx.x % kRedCols, qt = threadIdx.x / kRedCols;
     const int e = blockIdx.x * kRedCols + c;
-    const int g0 = (int)((int64_t)qt * G / 4), g1 = (int)((int64_t)(qt + 1) * G / 4);
+    const int g0 = (int)((int64_t)qt * G / kRedWaves), g1 = (int)((int64_t)(qt + 1) * G / kRedWaves);
     float s[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     if (e < PS) {
         int g = g0;
@@ -674,10 +849,12 @@ __global__ __launch_bounds__(kThreads) void ctr_reduce_k(const float *__restrict
     float sub = 0.f;
 #pragma unroll
     for (int r = 0; r < 8; ++r) sub += s[r];
-    q4[qt][c] = sub;
+    q16[qt][c] = sub;
     __syncthreads();
     if (qt != 0 || e >= PS) return;
-    const float tot = ((q4[0][c] + q4[1][c]) + q4[2][c]) + q4[3][c];
+    float tot = q16[0][c];
+#pragma unroll
+    for (int q = 1; q < kRedWaves; ++q) tot += q16[q][c];
     if (e == PS - 4) {
         *o.loss = tot / (float)o.B;
         return;
@@ -968,8 +1145,9 @@ extern "C" ams_status ams_ctr_fwd_bwd(const ams_ctr *net, int32_t B, int32_t n_f
     s = net_out(a, dW, db, dslope, 0, o);
     if (s != AMS_OK) return s;
     if (!labels || !loss) return AMS_ERR_NULL;
+    const CtrArgs *nets[] = {&a};
+    if (net_width_bytes(nets, 1) > lds_limit()) return AMS_ERR_DIMS;
     const size_t lds = ctr_lds_bytes(a);
-    if (lds > lds_limit()) return AMS_ERR_DIMS;
     const int G = (B + kCtrBS - 1) / kCtrBS;
     const int PS = net_part_size(a) + 4;
     if (!ws || ws_bytes < (size_t)G * PS * 4) return AMS_ERR_WORKSPACE;
@@ -978,7 +1156,7 @@ extern "C" ams_status ams_ctr_fwd_bwd(const ams_ctr *net, int32_t B, int32_t n_f
     AMS_LAUNCH("ctr_fwd_bwd", st, ctr_fb_k<<<G, kCtrThreads, lds, st>>>(a, B, labels, prob, part, PS));
     o.loss = loss;
     o.B = B;
-    AMS_LAUNCH("ctr_reduce", st, ctr_reduce_k<<<(PS + kRedCols - 1) / kRedCols, kThreads, 0, st>>>(part, G, PS, o));
+    AMS_LAUNCH("ctr_reduce", st, ctr_reduce_k<<<(PS + kRedCols - 1) / kRedCols, kRedThreads, 0, st>>>(part, G, PS, o));
     return ams_launch_status();
 }
 
@@ -1021,18 +1199,21 @@ extern "C" ams_status ams_dssm_fwd_bwd(const ams_ctr *user_net, const ams_ctr *a
     s = net_out(v, dWa, dba, dslope_a, net_part_size(u), o);
     if (s != AMS_OK) return s;
     if (!labels || !loss) return AMS_ERR_NULL;
-    const size_t lds = (size_t)(2 * ctr_act_floats(u) + 2 * ctr_act_floats(v) +
-                                max(ctr_scr_floats(u), ctr_scr_floats(v)) + kCtrBS) * 4;
+    const CtrArgs *nets[] = {&u, &v};
+    if (net_width_bytes(nets, 2) > lds_limit()) return AMS_ERR_DIMS;
+    const bool tight = dssm_lds_bytes(u, v, false) > lds_limit();
+    const size_t lds = dssm_lds_bytes(u, v, tight);
     if (lds > lds_limit()) return AMS_ERR_DIMS;
     const int G = (B + kCtrBS - 1) / kCtrBS;
     const int PS = net_part_size(u) + net_part_size(v) + 4;
     if (!ws || ws_bytes < (size_t)G * PS * 4) return AMS_ERR_WORKSPACE;
     hipStream_t st = (hipStream_t)stream;
     float *part = (float *)ws;
-    AMS_LAUNCH("dssm_fwd_bwd", st, dssm_fb_k<<<G, kCtrThreads, lds, st>>>(u, v, B, labels, prob, part, PS));
+    AMS_LAUNCH("dssm_fwd_bwd", st, dssm_fb_k<<<G, kCtrThreads, lds, st>>>(TowerArgs{{u, v}}, tight, B, labels, prob, part,
+                                                                           PS));
     o.loss = loss;
     o.B = B;
-    AMS_LAUNCH("ctr_reduce", st, ctr_reduce_k<<<(PS + kRedCols - 1) / kRedCols, kThreads, 0, st>>>(part, G, PS, o));
+    AMS_LAUNCH("ctr_reduce", st, ctr_reduce_k<<<(PS + kRedCols - 1) / kRedCols, kRedThreads, 0, st>>>(part, G, PS, o));
     return ams_launch_status();
 }
 
