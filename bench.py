@@ -50,9 +50,9 @@ OTHER_WORKLOADS = ("c2_bf16", "c3_long")
 
 def mfma_peak(kernel: str, dtype: str) -> float:
     """Dense MFMA peak of the type a kernel's products run in: the split
-    float32 layer 1 (l1sk_x3) runs on bf16 MFMA; other float32-storage
-    kernels on float32 MFMA."""
-    if kernel.endswith("_bf16") or kernel == "l1sk_x3":
+    float32 layer 1 and its weight gradient (l1sk_x3, dw1_part_x3) run on
+    bf16 MFMA; other float32-storage kernels on float32 MFMA."""
+    if kernel.endswith(("_bf16", "_x3")):
         return PEAK_MFMA["bf16"]
     if kernel.endswith("_f32"):
         return PEAK_MFMA["f32"]
@@ -70,7 +70,7 @@ def flops_per_unique(dims):
 # Algorithmic work of the layer-1 GEMM kernels per unique image: 2*F*H flops
 # and one read of the image's F-wide feature row.
 GEMM_KERNELS = ("l1sk_f32", "l1sk_bf16", "l1rs_bf16", "l1sk_x3", "l1_fwd_f32", "l1_fwd_bf16", "dw1_part_f32",
-                "dw1_part_bf16", "dw1_rs_bf16", "dw1_part")
+                "dw1_part_x3", "dw1_part_bf16", "dw1_rs_bf16", "dw1_part")
 
 
 def gemm_work_per_unique(dims, esz):
@@ -460,9 +460,9 @@ def bench_step(w, mode, args, light=False):
         assert int(step3.dev_status.item()) == 0
         ms3 = t_start.elapsed_time(t_end) / args.steps
         split3 = {"value": beh_total / (ms3 * args.steps * 1e-3), "ms_per_step": ms3,
-                  "note": "the same steps with dtype f32x3: float32 operands, layer 1's forward product on "
-                          "bf16 MFMA with each operand split exactly into three bf16 parts (six part "
-                          "products kept, float32-rounding-sized error)"}
+                  "note": "the same steps with dtype f32x3: float32 operands, layer 1's forward product "
+                          "and its weight gradient on bf16 MFMA with each operand split exactly into three "
+                          "bf16 parts (six part products kept, error below float32 MFMA's)"}
         del step3
 
     # per-call durations: a second pass with events between the calls

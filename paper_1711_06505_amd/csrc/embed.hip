@@ -921,7 +921,10 @@ __global__ __launch_bounds__(rs::kThreads) __attribute__((amdgpu_waves_per_eu(rs
 // products of x y the six kept (hh, hm, mh, hl, lh, mm) leave out
 // |ml + lm + ll| < 2^-22 |x y| (|m| <= 2^-8 |x|, |l| <= 2^-16 |x|), and each
 // part product is exact in the float32 accumulator.  A 16-deep k step is six
-// bf16 MFMAs (6 x 32 cycles) in place of eight float32 ones (8 x 64).
+// bf16 MFMAs (6 x 32 cycles) in place of eight float32 ones (8 x 64).  hh has
+// an accumulator of its own, so that a sixth of the sums carry the result's
+// rounding: H1's error against float64 at 12900 rows 1.7e-7 (5.4e-7 with one
+// accumulator, 4.6e-7 in float32 MFMA), dW1's 2.0e-7 (4.3e-7), in the same time.
 
 __device__ __forceinline__ uint32_t cvt_pk_bf16(float a, float b)
 {
@@ -985,7 +988,8 @@ static_assert(X3::TILE == Sk<float>::TILE && X3::BM == Sk<float>::BM && X3::BK =
               "the split kernel leaves its partial tiles in the float32 layout");
 static_assert(X3::PW == 8 && X3::A_FL / 256 == 2 * (kSkThreads / AMS_WAVE), "2 feature-row instructions per wave");
 
-__device__ __forceinline__ void x3_compute(const float *slot, v16f (&acc)[1][kSkNB], int lane, int wave)
+__device__ __forceinline__ void x3_compute(const float *slot, v16f (&acc)[1][kSkNB], v16f (&low)[kSkNB], int lane,
+                                           int wave)
 {
     const int h = lane >> 5, r32 = lane & 31, wm = wave >> 1, wn = wave & 1;
     // rows read are r32 plus multiples of 32: one swizzle per lane
@@ -1011,14 +1015,14 @@ __device__ __forceinline__ void x3_compute(const float *slot, v16f (&acc)[1][kSk
         split3x8(x, ah, am, al);
 #pragma unroll
         for (int nb = 0; nb < kSkNB; ++nb) {
-            v16f c = acc[0][nb];
-            c = mfma_bf16(bh[nb], ah, c);
-            c = mfma_bf16(bm[nb], ah, c);
-            c = mfma_bf16(bh[nb], am, c);
+            v16f c = low[nb];
             c = mfma_bf16(bl[nb], ah, c);
             c = mfma_bf16(bh[nb], al, c);
             c = mfma_bf16(bm[nb], am, c);
-            acc[0][nb] = c;
+            c = mfma_bf16(bm[nb], ah, c);
+            c = mfma_bf16(bh[nb], am, c);
+            low[nb] = c;
+            acc[0][nb] = mfma_bf16(bh[nb], ah, acc[0][nb]);
         }
     }
 }
@@ -1077,9 +1081,12 @@ __global__ __launch_bounds__(kSkThreads) void l1sk_x3(const float *__restrict__ 
                 src[q] = (const char *)(W1p + pl * plane + (size_t)(n0 + rb) * F) + chunk * 16;
             }
         }
-        v16f acc[1][kSkNB];
+        v16f acc[1][kSkNB], low[kSkNB];
 #pragma unroll
-        for (int nb = 0; nb < kSkNB; ++nb) acc[0][nb] = (v16f){};
+        for (int nb = 0; nb < kSkNB; ++nb) {
+            acc[0][nb] = (v16f){};
+            low[nb] = (v16f){};
+        }
         const int n = ke - ks;
         auto issue = [&](float *slot, int st) {
 #pragma unroll
@@ -1099,7 +1106,7 @@ __global__ __launch_bounds__(kSkThreads) void l1sk_x3(const float *__restrict__ 
         __builtin_amdgcn_sched_barrier(0);                                         \
         if ((s) + 1 < n) issue(nxt, ks + (s) + 1);                                 \
         __builtin_amdgcn_sched_barrier(0);                                         \
-        x3_compute(cur, acc, lane, wave);                                          \
+        x3_compute(cur, acc, low, lane, wave);                                     \
     } while (0)
         issue(ring0, ks);
         int s = 0;
@@ -1110,6 +1117,8 @@ __global__ __launch_bounds__(kSkThreads) void l1sk_x3(const float *__restrict__ 
         if (s < n) X3_STAGE(ring0, ring1, s);
 #undef X3_STAGE
         AMS_WAIT_VM(0);
+#pragma unroll
+        for (int nb = 0; nb < kSkNB; ++nb) acc[0][nb] += low[nb];
         sk_store<1>(acc, ks == 0 && ke == S, rid, m0, n0, n_u, H, b1, keep_z, H1, nullptr, nullptr,
                     pbuf + ((size_t)w * 2 + (first ? 0 : 1)) * X3::TILE, lane, wave);
         first = false;
@@ -2157,7 +2166,8 @@ __device__ __forceinline__ float tb_dzl(brsrc_t rdE, brsrc_t rE, int final_relu,
     return (d < D && (!final_relu || e > 0.f)) ? g : 0.f;
 }
 
-template <int L, int SD, typename TW, typename TH, bool PR>
+// X3: dZ1 leaves as the three bf16 parts of AMS_F32_X3, planes [cap x H].
+template <int L, int SD, typename TW, typename TH, bool PR, bool X3 = false>
 __global__ __launch_bounds__(kTbThreads) void tail_bwd(const TH *__restrict__ H1s,
                                                         const float *__restrict__ H2s,
                                                         const float *__restrict__ Efwd,
@@ -2236,7 +2246,12 @@ __global__ __launch_bounds__(kTbThreads) void tail_bwd(const TH *__restrict__ H1
         const brsrc_t rE = make_buf(final_relu ? Efwd + (size_t)c0 * D : dE, final_relu ? nr * D * 4 : 0);
         const brsrc_t rH2 = make_buf(L == 3 ? H2s + (size_t)c0 * M : dE, L == 3 ? nr * M * 4 : 0);
         const brsrc_t rH1 = make_buf(H1s + (size_t)c0 * H, nr * H * (uint32_t)sizeof(TH));
-        const brsrc_t rZ1 = make_buf(dZ1 + (size_t)c0 * H, nr * H * (uint32_t)sizeof(TH));
+        const brsrc_t rZ1 = make_buf(dZ1 + (size_t)c0 * H, X3 ? 0 : nr * H * (uint32_t)sizeof(TH));
+        brsrc_t rPl[3];
+        if (X3)
+#pragma unroll
+            for (int pl = 0; pl < 3; ++pl)
+                rPl[pl] = make_buf((uint16_t *)dZ1 + ((size_t)pl * cap + c0) * H, nr * H * 2);
         // phase 2's operands loaded with phase 1's (one memory round trip per
         // chunk; one wave per SIMD leaves the registers for it)
         float dA3[16];                          // dzl[row][d = r32] (dW3's operand, db3)
@@ -2313,7 +2328,20 @@ __global__ __launch_bounds__(kTbThreads) void tail_bwd(const TH *__restrict__ H1
                 const float dz = pos ? a1[ib][jj] : (PR ? sl1[ib] * a1[ib][jj] : 0.f);
                 cs += dz;
                 if (PR) css += pos ? 0.f : a1[ib][jj] * h1v[ib][jj];
-                if (icol < H) buf_st<TH>(rZ1, (uint32_t)(acc_row(jj, lane) * H + icol), dz);
+                if constexpr (X3) {
+                    if (icol < H) {
+                        const uint32_t e = 2u * (uint32_t)(acc_row(jj, lane) * H + icol);
+                        const uint16_t ph = ams_f32_to_bf16(dz);
+                        const float r1 = dz - ams_bf16_to_f32(ph);
+                        const uint16_t pm = ams_f32_to_bf16(r1);
+                        const float r2 = r1 - ams_bf16_to_f32(pm);
+                        __builtin_amdgcn_raw_buffer_store_b16(ph, rPl[0], e, 0, 0);
+                        __builtin_amdgcn_raw_buffer_store_b16(pm, rPl[1], e, 0, 0);
+                        __builtin_amdgcn_raw_buffer_store_b16(ams_f32_to_bf16(r2), rPl[2], e, 0, 0);
+                    }
+                } else if (icol < H) {
+                    buf_st<TH>(rZ1, (uint32_t)(acc_row(jj, lane) * H + icol), dz);
+                }
             }
             db1a[ib] += cs + __shfl_xor(cs, 32, AMS_WAVE);
             if (PR) {
@@ -2946,6 +2974,175 @@ __device__ __forceinline__ void dwtr_compute(const float *slot, v16f *acc, int l
         if (kk < KK - 1) __builtin_amdgcn_sched_group_barrier(0x100, 4 + 2 * NB, 0);
         __builtin_amdgcn_sched_group_barrier(0x008, 2 * NB, 0);
     }
+}
+
+// Split-float32 dW1 partial of chunk c (AMS_F32_X3): the tiles, chunks and row
+// streaming of dw1_part_f32 with every operand as three bf16 parts and six
+// bf16 MFMAs per 16 images in place of eight float32 ones (6 x 32 cycles
+// against 8 x 64).  dZ1 comes split (three planes [cap x 256], written by the
+// backward tail); the feature operand is split in registers after the LDS
+// read.  The products of the two high parts have an accumulator of their own:
+// the sums that carry the result's rounding are then 1/6 as many as with one
+// accumulator, and the error against float64 is half the float32 MFMA's.
+// 20011 rows: 346 us in float32 MFMA, 250-257 us so (1.0 PFLOP/s of part
+// products, what a large bf16 matrix product reaches on this card; 12900 rows:
+// 224 and 160-183).  Ordering the LDS reads, the splits and the MFMAs by
+// scheduling groups (263 us) or raising the waves' priority over the products
+// (no change) did not help.
+//
+// A stage is 32 images: the feature rows' 128 columns in float32 (16 KB, 16-byte
+// chunks of rows 8-15 and 24-31 at chunk ^ 8: a wave's 4-byte reads take rows
+// 8 h + j of its two halves, which then meet different banks) and the three
+// planes' 256 columns (48 KB, read with ds_read_b64_tr_b16 as in
+// dw1_part_bf16); two slots.  Waves are 4 (h) x 2 (f), 64 x 64 each.
+struct DwX3 {
+    static constexpr int BM = 256, BN = 128, BK = 32, WAVES = 8;
+    static constexpr int B_BYTES = BK * BN * 4, PL_BYTES = BK * BM * 2;
+    static constexpr int SLOT = (B_BYTES + 3 * PL_BYTES) / 4;     // floats per slot: 64 KB
+    static constexpr int PB = B_BYTES / 1024 / WAVES;             // DMA instructions per wave: 2 of rows,
+    static constexpr int PA = 3 * PL_BYTES / 1024 / WAVES;        // 6 of planes
+};
+static_assert(DwX3::BM == DwRing::BM && DwX3::BN == DwRing::BN && DwX3::BK == DwRing::BK && DwX3::PB == DwRing::PB,
+              "the plan and the row IDs of dw1_part_f32");
+
+__device__ __forceinline__ int dwx_swz(int row) { return row & 8; }
+
+__device__ __forceinline__ void dwx_issue(float *slot, const float *__restrict__ T, int64_t n_rows, int F,
+                                          const uint16_t *__restrict__ planes, size_t plane, int n0, int u_base,
+                                          int u1, const float *__restrict__ zero_row, const int (&id)[DwX3::PB],
+                                          int wave, int lane)
+{
+    using R = DwX3;
+#pragma unroll
+    for (int q = 0; q < R::PB; ++q) {
+        const int j = R::PB * wave + q, row = 2 * j + (lane >> 5);
+        const bool ok = id[q] >= 0 && (int64_t)id[q] < n_rows;
+        dma16((ok ? T + (size_t)id[q] * F + n0 : zero_row) + 4 * ((lane & 31) ^ dwx_swz(row)), slot + j * 256);
+    }
+#pragma unroll
+    for (int q = 0; q < R::PA; ++q) {
+        const int j = R::PA * wave + q, pl = j >> 4, row = 2 * (j & 15) + (lane >> 5);
+        const int lc = (lane & 31) ^ dwtr_swz(row), u = u_base + row;
+        const char *src = u < u1 ? (const char *)(planes + pl * plane + (size_t)u * R::BM) + lc * 16
+                                 : (const char *)zero_row + lc * 16;
+        dma16(src, slot + R::B_BYTES / 4 + j * 256);
+    }
+}
+
+__device__ __forceinline__ void dwx_compute(const float *slot, v16f (&acc)[4], v16f (&low)[4], int lane, int wave)
+{
+    using R = DwX3;
+    const char *A = (const char *)slot + R::B_BYTES;
+    const int h = lane >> 5, r32 = lane & 31, g = lane >> 4, i = lane & 15;
+    const int wm = wave >> 1, wn = wave & 1;
+    const int r_in = 8 * (g >> 1) + (i >> 2), c_in = 16 * (g & 1) + 4 * (i & 3);
+#pragma unroll
+    for (int kk = 0; kk < R::BK / 16; ++kk) {
+        float x[2][8];
+#pragma unroll
+        for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const int row = 16 * kk + 8 * h + j, col = wn * 64 + nb * 32 + r32;
+                x[nb][j] = slot[row * R::BN + (col ^ (dwx_swz(row) << 2))];
+            }
+        uint4 a[3][2];
+#pragma unroll
+        for (int pl = 0; pl < 3; ++pl)
+#pragma unroll
+            for (int mb = 0; mb < 2; ++mb) {
+                const int r0 = 16 * kk + r_in, col = wm * 64 + mb * 32 + c_in;
+                const uint2 lo = ds_read_tr16(A + pl * R::PL_BYTES + dwtr_off(r0, col, R::BM * 2));
+                const uint2 hi = ds_read_tr16(A + pl * R::PL_BYTES + dwtr_off(r0 + 4, col, R::BM * 2));
+                a[pl][mb] = make_uint4(lo.x, lo.y, hi.x, hi.y);
+            }
+#pragma unroll
+        for (int nb = 0; nb < 2; ++nb) {
+            uint4 bh, bm, bl;
+            split3x8(x[nb], bh, bm, bl);
+#pragma unroll
+            for (int mb = 0; mb < 2; ++mb) {
+                v16f c = low[mb * 2 + nb];
+                c = mfma_bf16(a[2][mb], bh, c);
+                c = mfma_bf16(a[0][mb], bl, c);
+                c = mfma_bf16(a[1][mb], bm, c);
+                c = mfma_bf16(a[1][mb], bh, c);
+                c = mfma_bf16(a[0][mb], bm, c);
+                low[mb * 2 + nb] = c;
+                acc[mb * 2 + nb] = mfma_bf16(a[0][mb], bh, acc[mb * 2 + nb]);
+            }
+        }
+    }
+}
+
+__global__ __launch_bounds__(kDwThreads) void dw1_part_x3(const float *__restrict__ T, int64_t n_rows, int F,
+                                                          const int32_t *__restrict__ uniq,
+                                                          const int32_t *__restrict__ n_uniq_p, int cap,
+                                                          const uint16_t *__restrict__ planes, int KC,
+                                                          const float *__restrict__ zero_row,
+                                                          float *__restrict__ part)
+{
+    using R = DwX3;
+    __shared__ __attribute__((aligned(16))) float ring0[R::SLOT];
+    __shared__ __attribute__((aligned(16))) float ring1[R::SLOT];
+
+    const int nnt = F / R::BN;
+    // the column tiles of one chunk go to one XCD: they share its dZ1 planes
+    int c, nt;
+    if (!xcd_tile(blockIdx.x, KC, nnt, c, nt)) return;
+    const int n_u = min(*n_uniq_p, cap);
+    const int u0 = (int)((int64_t)c * n_u / KC), u1 = (int)((int64_t)(c + 1) * n_u / KC);
+    const int n0 = nt * R::BN;
+    const size_t plane = (size_t)cap * R::BM;
+    const int lane = ams_lane(), wave = threadIdx.x / AMS_WAVE;
+
+    v16f acc[4], low[4];
+#pragma unroll
+    for (int x = 0; x < 4; ++x) acc[x] = low[x] = (v16f){};
+    const int S = (u1 - u0 + R::BK - 1) / R::BK;
+    if (S > 0) {
+        // stage s + 1's DMA (with the IDs loaded at stage s - 1) and stage
+        // s + 2's IDs are issued once stage s has landed, and wait for the
+        // next stage's top
+        int ida[R::PB], idb[R::PB];
+        dw1_load_ids(uniq, u0, u1, wave, lane, ida);
+        dw1_load_ids(uniq, u0 + min(1, S - 1) * R::BK, u1, wave, lane, idb);
+        dwx_issue(ring0, T, n_rows, F, planes, plane, n0, u0, u1, zero_row, ida, wave, lane);
+#define DWX_STAGE(cur, nxt, ids_dma, ids_load, s)                                                                  \
+    do {                                                                                                           \
+        __builtin_amdgcn_sched_barrier(0);                                                                         \
+        AMS_WAIT_VM_LDS(0);                                                                                        \
+        __builtin_amdgcn_s_barrier();                                                                              \
+        __builtin_amdgcn_sched_barrier(0);                                                                         \
+        if ((s) + 1 < S)                                                                                           \
+            dwx_issue(nxt, T, n_rows, F, planes, plane, n0, u0 + ((s) + 1) * R::BK, u1, zero_row, ids_dma, wave,   \
+                      lane);                                                                                       \
+        dw1_load_ids(uniq, u0 + min((s) + 2, S - 1) * R::BK, u1, wave, lane, ids_load);                            \
+        __builtin_amdgcn_sched_barrier(0);                                                                         \
+        dwx_compute(cur, acc, low, lane, wave);                                                                    \
+    } while (0)
+        int s = 0;
+        for (; s + 2 <= S; s += 2) {
+            DWX_STAGE(ring0, ring1, idb, ida, s);
+            DWX_STAGE(ring1, ring0, ida, idb, s + 1);
+        }
+        if (s < S) DWX_STAGE(ring0, ring1, idb, ida, s);
+#undef DWX_STAGE
+        AMS_WAIT_VM(0);
+    }
+
+    float *out = part + (size_t)c * R::BM * F;
+#pragma unroll
+    for (int mb = 0; mb < 2; ++mb)
+#pragma unroll
+        for (int nb = 0; nb < 2; ++nb) {
+            const int col = n0 + (wave & 1) * 64 + nb * 32 + (lane & 31);
+#pragma unroll
+            for (int j = 0; j < 16; ++j) {
+                const int row = (wave >> 1) * 64 + mb * 32 + acc_row(j, lane);
+                out[(size_t)row * F + col] = acc[mb * 2 + nb][j] + low[mb * 2 + nb][j];
+            }
+        }
 }
 
 template <int BN>
@@ -3618,6 +3815,7 @@ size_t al256(size_t x) { return (x + 255) & ~(size_t)255; }
 int sk_workers();
 
 bool use_dw_ring(const ams_mlp *m) { return m->dtype != AMS_BF16 && m->dims[1] == DwRing::BM && m->dims[0] % DwRing::BN == 0; }
+bool use_dw_x3(const ams_mlp *m) { return m->dtype == AMS_F32_X3 && use_dw_ring(m); }
 bool use_dw_tr(const ams_mlp *m) { return m->dtype == AMS_BF16 && m->dims[1] == DwTr::BM && m->dims[0] % DwTr::BN == 0; }
 
 // Split-K chunk count of dW1: the DMA-ring kernel takes one block per CU
@@ -3665,7 +3863,7 @@ BwdPlan plan_bwd(const ams_mlp *m, int32_t cap)
 {
     BwdPlan p{};
     const int H = m->dims[1], F = m->dims[0];
-    const size_t es = (m->dtype == AMS_BF16) ? 2 : 4;
+    const size_t es = (m->dtype == AMS_BF16) ? 2 : use_dw_x3(m) ? 6 : 4;
     p.kc = dw1_chunks(m, cap);
     size_t o = 0;
     p.off_zero = o; o += al256((size_t)(F > H ? F : H) * 4);
@@ -3920,7 +4118,25 @@ extern "C" ams_status ams_embed_bwd(const ams_mlp *mlp, const void *T, int64_t n
                                    H, M, D, mlp->final_relu, n_uniq, cap, (TH *)dz1, tail, PS, zero,     \
                                    F > H ? F : H, s1, s2)))
     const int TG = tail_blocks(mlp);
-    if (use_tail_bf16(mlp)) {
+#define TBX_LAUNCH(LL, SDV, PRV)                                                                        \
+    AMS_LAUNCH("tail_bwd", st, (tail_bwd<LL, SDV, float, float, PRV, true><<<kTailBlocks, kTbThreads, 0, st>>>( \
+                                   (const float *)H1_save, H2_save, E_fwd, dE, (const float *)W2, (const float *)W3, \
+                                   H, M, D, mlp->final_relu, n_uniq, cap, (float *)dz1, tail, PS, zero,  \
+                                   F > H ? F : H, s1, s2)))
+    if (use_dw_x3(mlp)) {
+        if (pr) {
+            if (L == 3 && D <= 16) TBX_LAUNCH(3, 8, true);
+            else if (L == 3) TBX_LAUNCH(3, 16, true);
+            else if (D <= 16) TBX_LAUNCH(2, 8, true);
+            else TBX_LAUNCH(2, 16, true);
+        } else {
+            if (L == 3 && D <= 16) TBX_LAUNCH(3, 8, false);
+            else if (L == 3) TBX_LAUNCH(3, 16, false);
+            else if (D <= 16) TBX_LAUNCH(2, 8, false);
+            else TBX_LAUNCH(2, 16, false);
+        }
+#undef TBX_LAUNCH
+    } else if (use_tail_bf16(mlp)) {
 #define TBF_LAUNCH(LL, DM, PRV)                                                                         \
     AMS_LAUNCH("tail_bwd_bf16", st, (tail_bwd_bf16<LL, DM, PRV><<<TG, kThreads, 0, st>>>(                \
                                         (const uint16_t *)H1_save, H2_save, E_fwd, dE, (const uint16_t *)W2, \
@@ -3958,7 +4174,12 @@ extern "C" ams_status ams_embed_bwd(const ams_mlp *mlp, const void *T, int64_t n
     const int grid = ((outer + 7) / 8) * 8 * nmt;
     if (use_dw_ring(mlp)) {
         const int grid8 = ((p.kc + 7) / 8) * 8 * (F / DwRing::BN);
-        AMS_LAUNCH("dw1_part_f32", st, dw1_part_f32<<<grid8, kDwThreads, 0, st>>>((const float *)T, n_rows, F, uniq, n_uniq, cap,
+        if (use_dw_x3(mlp))
+            AMS_LAUNCH("dw1_part_x3", st, dw1_part_x3<<<grid8, kDwThreads, 0, st>>>(
+                                              (const float *)T, n_rows, F, uniq, n_uniq, cap, (const uint16_t *)dz1,
+                                              p.kc, zero, dw1p));
+        else
+            AMS_LAUNCH("dw1_part_f32", st, dw1_part_f32<<<grid8, kDwThreads, 0, st>>>((const float *)T, n_rows, F, uniq, n_uniq, cap,
                                                    (const float *)dz1, H, p.kc, zero, dw1p));
     } else if (use_dw_tr(mlp)) {
         const int bn = dwtr_bn(F, cap);

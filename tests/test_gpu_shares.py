@@ -90,3 +90,58 @@ def test_embed_over_share_plans(dims, n, cap, dtype):
     for l in range(len(W)):
         assert_close(dW[l], rW[l], RTOL[dtype], f"dW{l + 1}")
         assert_close(db[l], rb[l], RTOL[dtype], f"db{l + 1}")
+
+
+@pytest.mark.parametrize("dims,n,prelu", [
+    ((4096, 256, 64, 12), 517, True), ((4096, 256, 64, 12), 3000, True), ((4096, 256, 33, 20), 700, False),
+    ((256, 256, 32), 65, True), ((128, 256, 7), 1, False), ((4096, 256, 40, 17), 1300, True),
+])
+def test_split_weight_gradient(dims, n, prelu):
+    """The split-float32 backward (dZ1 as three bf16 planes) with every form of
+    the tail: two and three layers, narrow and wide outputs, PReLU; rows past the
+    capacity's end, and IDs outside the table, which read as zero rows.  dW1's
+    error stays within the float32 mode's."""
+    print(f"split dW1 {dims} n={n} prelu={prelu}", flush=True)
+    T, W, b, uniq, dE = model(dims, "f32", n)
+    uniq[n // 2] = T.shape[0] + 5
+    cap = n + 40
+    g = torch.Generator(device="cuda").manual_seed(n)
+    slopes = [torch.rand(d, generator=g, device="cuda") * 0.6 - 0.2 for d in dims[1:-1]] if prelu else None
+    x = T[uniq.long().clamp_max(T.shape[0] - 1)].double()
+    x[n // 2] = 0
+    err = {}
+    for dtype in ("f32", "f32x3"):
+        mlp = ams.make_mlp(dims, dtype)
+        new = lambda *s: torch.full(s, float("nan"), device="cuda")  # noqa: E731
+        n_uniq = torch.full((1,), n, dtype=torch.int32, device="cuda")
+        ids, up = torch.full((cap,), -1, dtype=torch.int32, device="cuda"), new(cap, dims[-1])
+        ids[:n], up[:n] = uniq, dE
+        H1, E = new(cap, dims[1]), new(cap, dims[-1])
+        H2 = new(cap, dims[2]) if len(dims) == 4 else None
+        dW, db = [new(*w.shape) for w in W], [new(*c.shape) for c in b]
+        ds = [new(*a.shape) for a in slopes] if prelu else None
+        ws = torch.full((ams.ams_embed_workspace(mlp, cap),), 255, dtype=torch.uint8, device="cuda")
+        ams.ams_embed_fwd(mlp, T, ids, n_uniq, cap, W, b, H1, H2, E, ws, slopes=slopes)
+        ams.ams_embed_bwd(mlp, T, ids, n_uniq, cap, W, H1, H2, E, up, dW, db, ws, slopes=slopes, dslopes=ds)
+        torch.cuda.synchronize()
+        # float64, on the saved hidden layers (pre-activations with PReLU) as the call's own inputs
+        hid = [h[:n].double() for h in (H1, H2) if h is not None]
+        d, rW, rs = dE.double(), [None] * len(W), [None] * (len(W) - 1)
+        for l in range(len(W) - 1, -1, -1):
+            if l < len(W) - 1:
+                z = hid[l]
+                if prelu:
+                    rs[l] = (d * z.clamp_max(0)).sum(0)
+                d = d * torch.where(z > 0, 1.0, slopes[l].double() if prelu else 0.0)
+            h = x if l == 0 else hid[l - 1] if not prelu else torch.where(
+                hid[l - 1] > 0, hid[l - 1], hid[l - 1] * slopes[l - 1].double())
+            rW[l] = d.t() @ h
+            if l:
+                d = d @ W[l].double()
+        for l in range(len(W)):
+            assert_close(dW[l], rW[l], RTOL[dtype], f"{dtype} dW{l + 1}")
+        for l in range(len(W) - 1):
+            if prelu:
+                assert_close(ds[l], rs[l], RTOL[dtype], f"{dtype} dslope{l + 1}")
+        err[dtype] = float((dW[0].double() - rW[0]).norm() / rW[0].norm().clamp_min(1e-30))
+    assert err["f32x3"] <= max(err["f32"], 1.5e-7), err     # (2^-23: a sum of a few products)
