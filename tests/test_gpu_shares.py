@@ -78,7 +78,8 @@ PAPER, SMALL = (4096, 256, 64, 12), (256, 256, 9)
     (PAPER, 12900, 12900),      # 101 tiles: two shares each in bf16 (202 workers)
     (PAPER, 18001, 18001),      # 141 tiles: shares cross tile boundaries in every type
     (PAPER, 30000, 30000),      # 235 tiles: one whole tile per worker in bf16
-    (SMALL, 1, 5), (SMALL, 257, 300), (SMALL, 4000, 4000),
+    (PAPER, 8192, 8192), (PAPER, 8193, 8193),   # tail backward: 256 blocks of 32 rows, 129 of 64
+    (SMALL, 1, 5), (SMALL, 257, 300), (SMALL, 4000, 4000), (SMALL, 8193, 8200),
 ])
 def test_embed_over_share_plans(dims, n, cap, dtype):
     print(f"shares {dims} n={n} cap={cap} {dtype}", flush=True)
