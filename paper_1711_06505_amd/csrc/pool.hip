@@ -10,8 +10,9 @@
 // normalises the stored logits into weights.
 //
 // Backward: (1) one wave per sample computes the per-sample terms of the
-// attention gradient and tags every behavior occurrence with its sample;
-// (2) one wave per chunk of 64 positions of the stable occurrence order
+// attention gradient, packs the rows its occurrences' gradients are made of
+// and records every occurrence's row and factors; (2) one wave per chunk of 64
+// positions of the stable occurrence order gathers the records and rows,
 // evaluates each occurrence's embedding gradient and sums runs of equal
 // unique image with a segmented lane scan on DPP moves -- runs wholly inside the chunk go
 // straight to dE, runs that cross a chunk edge leave a partial; (3) one wave
@@ -59,6 +60,21 @@ __device__ __forceinline__ void load_row(const float *__restrict__ E, int row, i
     }
 }
 
+// A row of D floats read as DM/4 16-byte loads with no condition: D == DM
+// and 16-byte aligned rows (the fast path of the fix-up below).
+template <int DM>
+__device__ __forceinline__ void load_row_full(const float *__restrict__ p, float (&e)[DM])
+{
+#pragma unroll
+    for (int d4 = 0; d4 < DM / 4; ++d4) {
+        const float4 v = *(const float4 *)(p + 4 * d4);
+        e[4 * d4] = v.x;
+        e[4 * d4 + 1] = v.y;
+        e[4 * d4 + 2] = v.z;
+        e[4 * d4 + 3] = v.w;
+    }
+}
+
 // Row `row` of E when it is below the row count `cap`, else a zero row: a
 // caller whose capacity is below the real unique count gets unspecified
 // values, never an access past its buffers.
@@ -69,6 +85,55 @@ __device__ __forceinline__ void load_row_cap(const float *__restrict__ E, int ro
     else {
 #pragma unroll
         for (int d = 0; d < DM; ++d) e[d] = 0.f;
+    }
+}
+
+// 16 bytes per lane from per-lane addresses straight into LDS at dst + 16 lane.
+__device__ __forceinline__ void dma16(const void *src, void *dst)
+{
+    __builtin_amdgcn_global_load_lds(src, (__attribute__((address_space(3))) void *)dst, 16, 0, 0);
+}
+
+// A gather of one row per lane.  Read with one lane per row, each 16-byte load
+// touches 64 lines, and the vector memory pipeline returns about one of them
+// every two cycles (its data unit was busy 90 % of the stable-order pass that
+// read its rows so).  So LPR lanes read one packed row of 4 LPR floats,
+// 64 / LPR rows per load, straight into LDS, and each lane takes its own from
+// there.  Lane l's row starts at 4 LPR l floats; its piece p lies at
+// p ^ row_swz(l), which spreads a quarter-wave's reads over the banks.
+template <int LPR>
+__device__ __forceinline__ int row_swz(int r) { return (r / (16 / LPR)) & (LPR - 1); }
+
+template <int LPR>
+__device__ __forceinline__ void stage_rows(const float *__restrict__ pack, unsigned row, float *lds, int lane)
+{
+    constexpr int RPL = AMS_WAVE / LPR;                            // rows per load
+#pragma unroll
+    for (int q = 0; q < LPR; ++q) {
+        const int r = q * RPL + lane / LPR;                        // the lane whose row this lane reads
+        const unsigned src = (unsigned)__shfl((int)row, r, AMS_WAVE);
+        const int p = (lane % LPR) ^ row_swz<LPR>(r);
+        dma16(pack + ((size_t)src * LPR + p) * 4, lds + q * AMS_WAVE * 4);
+    }
+}
+
+// The rows staged by this wave have landed (no other wave reads them).
+__device__ __forceinline__ void staged()
+{
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __builtin_amdgcn_wave_barrier();
+}
+
+template <int LPR, int DM>
+__device__ __forceinline__ void staged_row(const float *lds, int lane, int p0, float (&e)[DM])
+{
+#pragma unroll
+    for (int d4 = 0; d4 < DM / 4; ++d4) {
+        const float4 v = *(const float4 *)(lds + (lane * LPR + ((p0 + d4) ^ row_swz<LPR>(lane))) * 4);
+        e[4 * d4] = v.x;
+        e[4 * d4 + 1] = v.y;
+        e[4 * d4 + 2] = v.z;
+        e[4 * d4 + 3] = v.w;
     }
 }
 
@@ -256,41 +321,71 @@ __global__ __launch_bounds__(kThreads) void pool_concat_fwd_k(int B, int D, int 
 }
 
 // The record of occurrence k, written in occurrence order for the stable-order
-// pass to read with one access: its unique index, and its sample i for a
-// behavior or -1 - i for the ad of sample i; with attention also the
-// behavior's weight w_j and its score gradient ds_j (float bits).
+// pass to read with one access: its unique index and the packed row its
+// gradient is made of (i for a behavior of sample i, B + i for its ad, -1 for
+// none); with attention also the factors of the row's two halves (float bits):
+// the behavior's weight w_j and score gradient ds_j, 1 and 1 for an ad.  The
+// concatenate aggregator has no packed rows: i, or -1 - i for the ad.
 template <int MODE>
 constexpr bool wide_rec() { return MODE == AMS_POOL_ATT || MODE == kPoolQuery; }
 
-// (1) per sample: the records of its occurrences; attention terms
-// c_i = g_i . u_i and da_i = sum_j ds_j e_j, ds_j = w_j (g_i . e_j - c_i).
-// Sum mode with a second upstream gradient of the ads (dA2): da_i = dA_i +
-// dA2_i, the ad rows' gradient the stable-order pass then reads.
+// The packed rows, B of the behaviors, then B of the ads: [upstream gradient]
+// (sum), and beside it the query row (attention), the argmax positions (max).
+// An ad's are [dA | the attention term da], or [dA | its own position], so that
+// one rule makes both kinds' gradients.  A row is whole 16-byte pieces within
+// whole cache lines: the stable-order pass reads it with kLpr lanes.
+template <int MODE, int DM>
+struct Pack {
+    static constexpr bool two = MODE != AMS_POOL_SUM && MODE != kPoolConcat;
+    static constexpr int row = (two ? 2 : 1) * (DM <= 16 ? 16 : 32);    // floats
+    static constexpr int lpr = row / 4;                                 // lanes (16-byte pieces) per row
+};
+
+// (1) per sample: the records of its occurrences and its packed rows; attention
+// terms c_i = g_i . u_i and da_i = sum_j ds_j e_j, ds_j = w_j (g_i . e_j - c_i)
+// (da: the query's gradient in the query mode).  An ad's upstream gradient is
+// dA_i + dA2_i where both are given.
 template <int MODE, int DM>
 __global__ __launch_bounds__(kThreads) void pool_bwd_sample(int B, int D, const int32_t *__restrict__ seg_off,
                                                             int64_t n_beh, const int32_t *__restrict__ inv, int cap,
                                                             const float *__restrict__ E,
                                                             const float *__restrict__ U,
-                                                            const float *__restrict__ wsaved,
+                                                            const float *__restrict__ A,
+                                                            const void *__restrict__ saved,
                                                             const float *__restrict__ dU,
-                                                            void *__restrict__ rec,
-                                                            float *__restrict__ cvec,
-                                                            float *__restrict__ da,
                                                             const float *__restrict__ dA,
-                                                            const float *__restrict__ dA2)
+                                                            const float *__restrict__ dA2,
+                                                            void *__restrict__ rec, float *__restrict__ pack,
+                                                            float *__restrict__ dQ)
 {
+    constexpr bool ATT = wide_rec<MODE>();
+    using P = Pack<MODE, DM>;
     const int lane = ams_lane();
     const int i = blockIdx.x * kWaves + threadIdx.x / AMS_WAVE;
     if (i >= B) return;
-    if (MODE == AMS_POOL_SUM && dA2 && lane < D)
-        da[(size_t)i * D + lane] = (dA ? dA[(size_t)i * D + lane] : 0.f) + dA2[(size_t)i * D + lane];
-    const int j0 = seg_off[i], j1 = seg_off[i + 1];
-    if (lane == 0) {
-        const int k = (int)(n_beh + i);
-        if (wide_rec<MODE>()) ((int4 *)rec)[k] = make_int4(inv[k], -1 - i, 0, 0);
-        else ((int2 *)rec)[k] = make_int2(inv[k], -1 - i);
+    const int k_ad = (int)(n_beh + i);
+    // lane d holds column d of the packed rows (loaded first, used last)
+    float col = 0.f, ad_col = 0.f;
+    if (MODE != kPoolConcat) {
+        const int d = lane < DM ? lane : lane - DM;
+        const size_t at = (size_t)i * D + d;
+        if (d < D && lane < DM) {
+            col = dU[at];
+            ad_col = dA ? dA[at] : 0.f;
+            if (dA2) ad_col += dA2[at];
+        } else if (P::two && d < D && lane < 2 * DM) {
+            col = ATT ? A[at] : __int_as_float(((const int32_t *)saved)[at]);
+            if (MODE == AMS_POOL_MAX) ad_col = __int_as_float(k_ad);
+        }
     }
-    if (!wide_rec<MODE>()) {
+    const int j0 = seg_off[i], j1 = seg_off[i + 1];
+    const int row_ad = MODE == kPoolConcat ? -1 - i : MODE == kPoolQuery ? -1 : (int)((unsigned)B + (unsigned)i);
+    if (lane == 0) {
+        const int one = __float_as_int(1.f);
+        if (ATT) ((int4 *)rec)[k_ad] = make_int4(inv[k_ad], row_ad, one, one);
+        else ((int2 *)rec)[k_ad] = make_int2(inv[k_ad], row_ad);
+    }
+    if (!ATT) {
         int2 *r2 = (int2 *)rec;
         int j = j0 + lane;
         for (; j + AMS_WAVE < j1; j += 2 * AMS_WAVE) {
@@ -300,7 +395,12 @@ __global__ __launch_bounds__(kThreads) void pool_bwd_sample(int B, int D, const 
         }
         if (j < j1) r2[j] = make_int2(inv[j], i);
     }
-    if (MODE != AMS_POOL_ATT && MODE != kPoolQuery) return;
+    if (MODE != kPoolConcat && lane < P::row) {
+        pack[(size_t)i * P::row + lane] = col;
+        if (!ATT) pack[((size_t)B + i) * P::row + lane] = ad_col;
+    }
+    if (!ATT) return;
+    const float *wsaved = (const float *)saved;
     float g[DM], u[DM];
     load_row<DM>(dU, i, D, g);
     load_row<DM>(U, i, D, u);
@@ -336,14 +436,18 @@ __global__ __launch_bounds__(kThreads) void pool_bwd_sample(int B, int D, const 
         load_row_cap<DM>(E, r0, cap, D, e0);
         take(j, r0, e0);
     }
-    float mine = 0.f;
+    float mine = 0.f;                       // da's column d in lane d (query) or lane DM + d
+    constexpr int at0 = MODE == kPoolQuery ? 0 : DM;
 #pragma unroll
     for (int d = 0; d < DM; ++d) {
         const float v = ams_wave_sum(acc[d]);
-        if (lane == d) mine = v;
+        if (lane == at0 + d) mine = v;
     }
-    if (lane < D) da[(size_t)i * D + lane] = mine;
-    if (lane == 0) cvec[i] = c;
+    if (MODE == kPoolQuery) {
+        if (lane < D) dQ[(size_t)i * D + lane] = mine;
+    } else if (lane < P::row) {
+        pack[((size_t)B + i) * P::row + lane] = lane < DM ? ad_col : lane - DM < D ? mine : 0.f;
+    }
 }
 
 // One step of the segmented scan: every lane reads (key, values) of the lane
@@ -381,57 +485,62 @@ __device__ __forceinline__ void seg_scan(int u, float (&v)[DM])
     seg_step<0x143, 0xC, DM>(u, v);
 }
 
-// (2) segmented sums over chunks of 64 positions of the stable occurrence
-// order.  A wave takes CPW consecutive chunks and issues each level of their
-// dependent loads for all of them before using any (the stable order; then
-// each position's unique index and sample; then the rows), so CPW chains of
-// random reads are in flight per lane instead of one; each chunk is then
-// scanned and written as one.
 template <int MODE, int DM>
-constexpr int seg_cpw() { return DM > 16 || MODE == AMS_POOL_MAX ? 2 : 4; }
+constexpr int seg_cpw() { return MODE == kPoolConcat ? (DM > 16 ? 2 : 4) : 1; }
 
+// (2) segmented sums over chunks of 64 positions of the stable occurrence
+// order: three levels of dependent loads (the stable order; each position's
+// record; the rows), then a scan.  Bound by lines: a position's record is 16
+// bytes of a line of its own, and past the L2's 4 MB its sample's row is another
+// (12.07M positions, 65536 samples, attention: 18M lines of 128 bytes, 319 us =
+// 7.2 TB/s; with one lane per row, and rows of 48 bytes that straddle lines,
+// 443 us.  752k positions 26.9 -> 23.8 us, 2.2M 77.5 -> 54.2).  One chunk per
+// wave: two hold twice the LDS, so no more are in flight (341 us).  The
+// concatenate aggregator, whose rows are per position, reads them with one lane
+// per row, and on large grids a wave takes CPW chunks and issues each level for
+// all of them before using any.
 template <int MODE, int DM, int CPW>
 __global__ __launch_bounds__(kThreads) void pool_bwd_seg(int D, int n_occ, int cap,
                                                          const int32_t *__restrict__ occ_perm,
                                                          const int32_t *__restrict__ uniq_off,
-                                                         const float *__restrict__ A,
-                                                         const void *__restrict__ saved,
                                                          const float *__restrict__ dU,
                                                          const float *__restrict__ dA,
                                                          const void *__restrict__ rec,
-                                                         const float *__restrict__ da, int nch,
+                                                         const float *__restrict__ pack, int nch,
                                                          float *__restrict__ dE,
                                                          float *__restrict__ head_part,
                                                          float *__restrict__ tail_part,
                                                          int32_t *__restrict__ cross, int accumulate,
                                                          const int32_t *__restrict__ seg_off, int Lc)
 {
-    constexpr bool ATT = MODE == AMS_POOL_ATT || MODE == kPoolQuery;
+    constexpr bool ATT = wide_rec<MODE>(), CAT = MODE == kPoolConcat;
+    using P = Pack<MODE, DM>;
+    __shared__ __attribute__((aligned(16))) float stage[CAT ? 4 : kWaves * CPW * AMS_WAVE * P::row];
     const int lane = ams_lane();
-    const int ch0 = (blockIdx.x * kWaves + threadIdx.x / AMS_WAVE) * CPW;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / AMS_WAVE);
+    float *rows = stage + (CAT ? 0 : wave * CPW * AMS_WAVE * P::row);
+    int chv[CPW];                  // this wave's chunks (-1: none)
+    const int ch0 = (blockIdx.x * kWaves + wave) * CPW;
     if (ch0 >= nch) return;
+#pragma unroll
+    for (int c = 0; c < CPW; ++c) chv[c] = ch0 + c < nch ? ch0 + c : -1;
     // level 1: the stable order
     int k[CPW];
 #pragma unroll
     for (int c = 0; c < CPW; ++c) {
-        const int p = (ch0 + c) * AMS_WAVE + lane;
-        k[c] = p < n_occ ? occ_perm[p] : 0;
+        const int p = chv[c] * AMS_WAVE + lane;
+        k[c] = chv[c] >= 0 && p < n_occ ? occ_perm[p] : -1;
     }
-    // level 2: the record of each position's occurrence (unique index, sample,
-    // attention weight).  An occurrence whose unique index is at or past the
-    // caller's capacity (possible only when the capacity is below the real
-    // unique count) is dropped: its row of dE does not exist.  si: the sample
-    // of a behavior, -1 - i for the ad of sample i, or INT_MIN (nothing)
+    // level 2: the record of each position's occurrence
     int uk[CPW], si[CPW];
     float wk[CPW], dsk[CPW];
 #pragma unroll
     for (int c = 0; c < CPW; ++c) {
-        const int p = (ch0 + c) * AMS_WAVE + lane;
-        uk[c] = -1;
-        si[c] = INT_MIN;
+        uk[c] = INT_MAX;
+        si[c] = 0;
         wk[c] = 0.f;
         dsk[c] = 0.f;
-        if (p < n_occ) {
+        if (k[c] >= 0) {
             if constexpr (ATT) {
                 const int4 r = ((const int4 *)rec)[k[c]];
                 uk[c] = r.x;
@@ -445,65 +554,53 @@ __global__ __launch_bounds__(kThreads) void pool_bwd_seg(int D, int n_occ, int c
             }
         }
     }
-    // level 3: the rows each position's gradient is made of
-    float r[CPW][DM];            // dU of the behavior's sample (concat: its slice), or the ad's dA
-    float a[ATT ? CPW : 1][DM];  // attentive: the sample's query row, or the ad's attention term da
-    int am[MODE == AMS_POOL_MAX ? CPW : 1][DM];
+    // level 3: the rows each position's gradient is made of.  An occurrence
+    // whose unique index is at or past the caller's capacity (possible only
+    // when the capacity is below the real unique count) is dropped: its row of
+    // dE does not exist.
+    float r[CAT ? CPW : 1][DM];  // concat: the behavior's slice of dU, or the ad's dA
+    if constexpr (CAT) {
 #pragma unroll
-    for (int c = 0; c < CPW; ++c) {
-        const bool valid = si[c] != INT_MIN && uk[c] < cap;
-        const bool beh = valid && si[c] >= 0;
-        const bool ad = valid && si[c] < 0 && MODE != kPoolQuery;
-        const int i = beh ? si[c] : (ad ? -1 - si[c] : 0);
+        for (int c = 0; c < CPW; ++c) {
+            const bool valid = uk[c] < cap;
+            const int i = si[c] >= 0 ? si[c] : -1 - si[c];
 #pragma unroll
-        for (int d = 0; d < DM; ++d) r[c][d] = 0.f;
-        if (beh && MODE != kPoolConcat) load_row<DM>(dU, i, D, r[c]);
-        if (beh && MODE == kPoolConcat) {
-            const int pos = k[c] - seg_off[i];
-            if (pos < Lc) load_row<DM>(dU + (size_t)i * Lc * D, pos, D, r[c]);
+            for (int d = 0; d < DM; ++d) r[c][d] = 0.f;
+            if (valid && si[c] >= 0) {
+                const int pos = k[c] - seg_off[i];
+                if (pos < Lc) load_row<DM>(dU + (size_t)i * Lc * D, pos, D, r[c]);
+            }
+            if (valid && si[c] < 0 && dA) load_row<DM>(dA, i, D, r[c]);
         }
-        if (ad && dA) load_row<DM>(dA, i, D, r[c]);
-        if constexpr (MODE == AMS_POOL_MAX) {
-            const int32_t *amr = (const int32_t *)saved + (size_t)i * D;
+    } else {
 #pragma unroll
-            for (int d = 0; d < DM; ++d) am[c][d] = (beh && d < D) ? amr[d] : -1;
-        }
-        if constexpr (ATT) {
-#pragma unroll
-            for (int d = 0; d < DM; ++d) a[c][d] = 0.f;
-            if (beh) load_row<DM>(A, i, D, a[c]);
-            if (ad && MODE == AMS_POOL_ATT) load_row<DM>(da, i, D, a[c]);
-        }
+        for (int c = 0; c < CPW; ++c)
+            stage_rows<P::lpr>(pack, uk[c] < cap && si[c] != -1 ? (unsigned)si[c] : 0u,
+                               rows + c * AMS_WAVE * P::row, lane);
+        staged();
     }
     // each chunk: its positions' gradients, summed per run of one image
 #pragma unroll
     for (int c = 0; c < CPW; ++c) {
-        const int ch = ch0 + c;
-        if (ch >= nch) break;
+        const int ch = chv[c];
+        if (ch < 0) break;
         const int c0 = ch * AMS_WAVE, c1 = c0 + AMS_WAVE;
-        const bool valid = si[c] != INT_MIN && uk[c] < cap;
-        const bool beh = valid && si[c] >= 0;
+        const bool valid = uk[c] < cap;
         int u = valid ? uk[c] : -1 - lane;       // distinct per invalid lane: never joins a run
         float v[DM];
-#pragma unroll
-        for (int d = 0; d < DM; ++d) v[d] = 0.f;
-        if (beh) {
-            if (MODE == AMS_POOL_SUM || MODE == kPoolConcat) {
-#pragma unroll
-                for (int d = 0; d < DM; ++d) v[d] = r[c][d];
-            } else if (MODE == AMS_POOL_MAX) {
-#pragma unroll
-                for (int d = 0; d < DM; ++d) v[d] = am[MODE == AMS_POOL_MAX ? c : 0][d] == k[c] ? r[c][d] : 0.f;
-            } else {   // attentive: w_j g_i + ds_j a_i; A holds the query rows in the query mode
-#pragma unroll
-                for (int d = 0; d < DM; ++d) v[d] = wk[c] * r[c][d] + dsk[c] * a[ATT ? c : 0][d];
-            }
-        } else if (valid && MODE != kPoolQuery) {   // an ad: dA (+ the attention term)
+        if constexpr (CAT) {
 #pragma unroll
             for (int d = 0; d < DM; ++d) v[d] = r[c][d];
-            if (MODE == AMS_POOL_ATT) {
+        } else {
+            float x[DM], y[P::two ? DM : 4];
+            staged_row<P::lpr>(rows + c * AMS_WAVE * P::row, lane, 0, x);
+            if constexpr (P::two) staged_row<P::lpr>(rows + c * AMS_WAVE * P::row, lane, DM / 4, y);
+            const bool has = valid && si[c] != -1;   // (the query mode's ads have no gradient)
 #pragma unroll
-                for (int d = 0; d < DM; ++d) v[d] += a[ATT ? c : 0][d];
+            for (int d = 0; d < DM; ++d) {
+                if (ATT) v[d] = has ? wk[c] * x[d] + dsk[c] * y[P::two ? d : 0] : 0.f;
+                else if (MODE == AMS_POOL_MAX) v[d] = has && __float_as_int(y[P::two ? d : 0]) == k[c] ? x[d] : 0.f;
+                else v[d] = has ? x[d] : 0.f;
             }
         }
         seg_scan<DM>(u, v);
@@ -533,21 +630,6 @@ __global__ __launch_bounds__(kThreads) void pool_bwd_seg(int D, int n_occ, int c
         // only lane 63 can end a run that continues past the chunk
         const int cu = __shfl(cross_u, AMS_WAVE - 1, AMS_WAVE);
         if (lane == 0) cross[ch] = cu;
-    }
-}
-
-// A row of D floats read as DM/4 16-byte loads with no condition: D == DM
-// and 16-byte aligned rows (the fast path of the fix-up below).
-template <int DM>
-__device__ __forceinline__ void load_row_full(const float *__restrict__ p, float (&e)[DM])
-{
-#pragma unroll
-    for (int d4 = 0; d4 < DM / 4; ++d4) {
-        const float4 v = *(const float4 *)(p + 4 * d4);
-        e[4 * d4] = v.x;
-        e[4 * d4 + 1] = v.y;
-        e[4 * d4 + 2] = v.z;
-        e[4 * d4 + 3] = v.w;
     }
 }
 
@@ -620,8 +702,8 @@ template <int DM>
 constexpr int fix_short() { return DM > 16 ? 2 : 4; }
 
 // Below this many 64-position chunks the backward runs one chunk per wave
-// (stable-order pass and fix-up): the grid is then small enough that more
-// waves, not longer ones, keep the part busy.
+// (the concatenate aggregator's stable-order pass and the fix-up): the grid is
+// then small enough that more waves, not longer ones, keep the part busy.
 constexpr int kSmallChunks = 16384;
 
 // (3b) the fix-up of a run that starts in chunk ch and crosses chunk edges:
@@ -759,21 +841,21 @@ __global__ __launch_bounds__(kThreads) void pool_bwd_fix64(int D, int nch, bool 
 size_t al256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 struct PoolPlan {
-    size_t off_rec, off_c, off_da, off_head, off_tail, off_cross, off_bsum, total;
+    size_t off_rec, off_pack, off_head, off_tail, off_cross, off_bsum, total;
     int nch;
 };
 
 // Workspace of the backward; the records are 16 bytes with attention
-// (ams_pool_workspace's AMS_POOL_ATT also covers the query mode), 8 without.
-PoolPlan plan_pool(bool wide, int32_t B, int64_t n_beh, int32_t D)
+// (ams_pool_workspace's AMS_POOL_ATT also covers the query mode), 8 without;
+// two packed rows per sample, of 64 or 128 bytes per half.
+PoolPlan plan_pool(int32_t mode, int32_t B, int64_t n_beh, int32_t D)
 {
     PoolPlan p{};
     const int64_t n_occ = n_beh + B;
     p.nch = (int)((n_occ + AMS_WAVE - 1) / AMS_WAVE);
     size_t o = 0;
-    p.off_rec = o; o += al256((size_t)n_occ * (wide ? 16 : 8));
-    p.off_c = o; o += al256((size_t)B * 4);
-    p.off_da = o; o += al256((size_t)B * D * 4);
+    p.off_rec = o; o += al256((size_t)n_occ * (mode == AMS_POOL_ATT ? 16 : 8));
+    p.off_pack = o; o += al256((size_t)2 * B * (mode == AMS_POOL_SUM ? 1 : 2) * (D <= 16 ? 64 : 128));
     p.off_head = o; o += al256((size_t)p.nch * D * 4);
     p.off_tail = o; o += al256((size_t)p.nch * D * 4);
     p.off_cross = o; o += al256((size_t)p.nch * 4);
@@ -794,13 +876,11 @@ template <int MODE, int DM>
 void launch_bwd(int B, int D, const int32_t *seg_off, int64_t n_beh, const int32_t *inv, int cap,
                 const int32_t *occ_perm, const int32_t *uniq_off, const float *E, const float *U,
                 const float *A, const void *saved, const float *dU, const float *dA, float *dE,
-                char *ws, const PoolPlan &p, hipStream_t st, float *dQ = nullptr, int accumulate = 0,
-                int Lc = 0, const float *dA2 = nullptr)
+                char *ws, const PoolPlan &p, hipStream_t st, float *dQ = nullptr,
+                int accumulate = 0, int Lc = 0, const float *dA2 = nullptr)
 {
     void *rec = ws + p.off_rec;
-    float *cvec = (float *)(ws + p.off_c);
-    // the attention term of each sample: the query's gradient in the query mode
-    float *da = MODE == kPoolQuery ? dQ : (float *)(ws + p.off_da);
+    float *pack = (float *)(ws + p.off_pack);
     float *head = (float *)(ws + p.off_head);
     float *tail = (float *)(ws + p.off_tail);
     int32_t *cross = (int32_t *)(ws + p.off_cross);
@@ -811,15 +891,13 @@ void launch_bwd(int B, int D, const int32_t *seg_off, int64_t n_beh, const int32
     const bool full = D == DM;
     if (B > 0)
         AMS_LAUNCH("pool_bwd_sample", st, pool_bwd_sample<MODE, DM><<<(B + kWaves - 1) / kWaves, kThreads, 0, st>>>(
-            B, D, seg_off, n_beh, inv, cap, E, U, (const float *)saved, dU, rec, cvec, da, dA, dA2));
-    // sum mode with a second ad gradient: the ads read the folded rows
-    if (MODE == AMS_POOL_SUM && dA2) dA = da;
+            B, D, seg_off, n_beh, inv, cap, E, U, A, saved, dU, dA, dA2, rec, pack, dQ));
     const bool small = p.nch < kSmallChunks;
 #define SEG_LAUNCH(CPWV)                                                                                     \
     AMS_LAUNCH("pool_bwd_seg", st, (pool_bwd_seg<MODE, DM, CPWV><<<(p.nch + kWaves * CPWV - 1) / (kWaves * CPWV), \
                                                                   kThreads, 0, st>>>(                        \
-                                       D, n_occ, cap, occ_perm, uniq_off, A, saved, dU, dA, rec, da, p.nch, dE, \
-                                       head, tail, cross, accumulate, seg_off, Lc)))
+                                       D, n_occ, cap, occ_perm, uniq_off, dU, dA, rec, pack, p.nch, dE, head, tail, \
+                                       cross, accumulate, seg_off, Lc)))
     if (small) SEG_LAUNCH(1);
     else SEG_LAUNCH((seg_cpw<MODE, DM>()));
 #undef SEG_LAUNCH
@@ -874,7 +952,7 @@ extern "C" size_t ams_pool_workspace(int32_t mode, int32_t B, int64_t n_beh, int
 {
     (void)n_uniq_cap;
     if (check_common(mode, B, D, n_beh) != AMS_OK) return 0;
-    return plan_pool(mode == AMS_POOL_ATT, B, n_beh, D).total;
+    return plan_pool(mode, B, n_beh, D).total;
 }
 
 ams_status pool_bwd_sum_ads(int32_t B, int32_t D, const int32_t *seg_off, int64_t n_beh, const int32_t *inv,
@@ -887,13 +965,12 @@ ams_status pool_bwd_sum_ads(int32_t B, int32_t D, const int32_t *seg_off, int64_
     if (n_beh + B == 0) return AMS_OK;
     if (!seg_off || !inv || !occ_perm || !uniq_off || !dE) return AMS_ERR_NULL;
     if (B > 0 && !dU) return AMS_ERR_NULL;
-    const PoolPlan p = plan_pool(false, B, n_beh, D);
+    const PoolPlan p = plan_pool(AMS_POOL_SUM, B, n_beh, D);
     if (!ws || ws_bytes < p.total) return AMS_ERR_WORKSPACE;
     hipStream_t st = (hipStream_t)stream;
     with_dm(D, [&](auto dm) {
         launch_bwd<AMS_POOL_SUM, decltype(dm)::value>(B, D, seg_off, n_beh, inv, n_uniq_cap, occ_perm, uniq_off,
-                                                      nullptr, nullptr, nullptr, nullptr, dU, dA, dE, (char *)ws, p,
-                                                      st, nullptr, 0, 0, dA2);
+                                                      nullptr, nullptr, nullptr, nullptr, dU, dA, dE, (char *)ws, p, st, nullptr, 0, 0, dA2);
     });
     return ams_launch_status();
 }
@@ -913,7 +990,7 @@ extern "C" ams_status ams_pool_bwd(int32_t mode, int32_t B, int32_t D, const int
     if (!seg_off || !inv || !occ_perm || !uniq_off || !E || !dE) return AMS_ERR_NULL;
     if (B > 0 && (!U || !A || !dU)) return AMS_ERR_NULL;
     if (mode != AMS_POOL_SUM && B > 0 && !saved) return AMS_ERR_NULL;
-    const PoolPlan p = plan_pool(mode == AMS_POOL_ATT, B, n_beh, D);
+    const PoolPlan p = plan_pool(mode, B, n_beh, D);
     if (!ws || ws_bytes < p.total) return AMS_ERR_WORKSPACE;
     hipStream_t st = (hipStream_t)stream;
     char *w = (char *)ws;
@@ -966,7 +1043,7 @@ extern "C" ams_status ams_pool_query_bwd(int32_t B, int32_t D, const int32_t *se
     if (n_occ == 0) return AMS_OK;
     if (!seg_off || !inv || !occ_perm || !uniq_off || !E || !dE) return AMS_ERR_NULL;
     if (B > 0 && (!Q || !U || !w || !dU || !dQ)) return AMS_ERR_NULL;
-    const PoolPlan p = plan_pool(true, B, n_beh, D);
+    const PoolPlan p = plan_pool(AMS_POOL_ATT, B, n_beh, D);
     if (!ws || ws_bytes < p.total) return AMS_ERR_WORKSPACE;
     hipStream_t st = (hipStream_t)stream;
     char *wsc = (char *)ws;
@@ -1008,7 +1085,7 @@ extern "C" ams_status ams_pool_concat_bwd(int32_t B, int32_t D, int32_t Lc, cons
     if (n_occ == 0) return AMS_OK;
     if (!seg_off || !inv || !occ_perm || !uniq_off || !dE) return AMS_ERR_NULL;
     if (B > 0 && !dU) return AMS_ERR_NULL;
-    const PoolPlan p = plan_pool(false, B, n_beh, D);
+    const PoolPlan p = plan_pool(AMS_POOL_SUM, B, n_beh, D);
     if (!ws || ws_bytes < p.total) return AMS_ERR_WORKSPACE;
     hipStream_t st = (hipStream_t)stream;
     char *w = (char *)ws;
