@@ -346,8 +346,18 @@ __device__ __forceinline__ int sk_swz(int row)
 struct SkPlan {
     int n_u, n_cb, S, g;            // g = workers in use
     int64_t total;
-    __device__ int64_t it0(int w) const { return total * w / g; }
-    __device__ int owner(int64_t it) const { return (int)(((it + 1) * g - 1) / total); }
+    // (32-bit divisions where the products fit: a 64-bit one is some 150
+    // dependent instructions, and the kernels start with several)
+    __device__ bool fits32() const { return (total + 1) * g < ((int64_t)1 << 32); }
+    __device__ int64_t it0(int w) const
+    {
+        return fits32() ? (int64_t)((uint32_t)total * (uint32_t)w / (uint32_t)g) : total * w / g;
+    }
+    __device__ int owner(int64_t it) const
+    {
+        return fits32() ? (int)((((uint32_t)it + 1) * (uint32_t)g - 1) / (uint32_t)total)
+                        : (int)(((it + 1) * g - 1) / total);
+    }
 };
 
 // Workers in use.  With p whole shares per tile (p as many as the workers
@@ -1551,7 +1561,17 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
                 const int r = e / D, d = e % D;
                 if (c0 + r >= n_u) continue;
                 float v = b3s[d];
-                for (int oo = 0; oo < M; ++oo) v += W3s[d * (kMaxH2 + 1) + oo] * h2s[r][oo];
+                // 16 terms' reads in flight at once, added in order (M <= kMaxH2)
+                for (int o0 = 0; o0 < M; o0 += 16) {
+                    float a[16], b[16];
+#pragma unroll
+                    for (int x = 0; x < 16; ++x) {
+                        a[x] = W3s[d * (kMaxH2 + 1) + o0 + x];
+                        b[x] = h2s[r][o0 + x];
+                    }
+#pragma unroll
+                    for (int x = 0; x < 16; ++x) v = o0 + x < M ? v + a[x] * b[x] : v;
+                }
                 if (final_relu) v = fmaxf(v, 0.f);
                 E[(size_t)(c0 + r) * D + d] = v;
             }
@@ -1617,6 +1637,100 @@ __device__ __forceinline__ void split8(const float (&x)[8], uint4 &hi, uint4 &lo
     lo = make_uint4(pack_bf16(r[0], r[1]), pack_bf16(r[2], r[3]), pack_bf16(r[4], r[5]), pack_bf16(r[6], r[7]));
 }
 
+// The rest of a chunk after layer 2's products (acc[ob][j]: row lane % 32,
+// output 32 ob + acc_row(j, lane)): Z2 + b2 and its activation, stored to
+// H2_save (3 layers; Z2 itself with PReLU) or E (2 layers), then for 3
+// layers E = H2 W3^T + b3 on MFMA with W3 rows in LDS (kW3S bf16 apart), b3 in
+// LDS (zeros past D) and H2 split into hi and lo parts straight from the
+// registers.  Nothing here waits on global memory: with b3 read per output, W3
+// staged by a loop of conditional loads and the plan in 64-bit divisions, a
+// chunk's tail was a chain of round trips (12900 rows 20.2 us, 18.2 so; 64 rows
+// 19.5 and 17.0; 30000 rows 24.7 and 20.9).
+template <int L, bool PR>
+__device__ __forceinline__ void tfb_finish(const v16f (&acc)[2], const float (&bias)[2][16], bool relu2,
+                                           const uint16_t *W3s, const float *S2s, const float *B3s,
+                                           int final_relu, int M, int D, int row, bool live,
+                                           float *__restrict__ H2_save, float *__restrict__ E, int lane)
+{
+    const int h = lane >> 5, r32 = lane & 31;
+    float z[2][16];
+#pragma unroll
+    for (int ob = 0; ob < 2; ++ob)
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {
+            const float v = acc[ob][j] + bias[ob][j];
+            z[ob][j] = relu2 ? fmaxf(v, 0.f) : v;
+        }
+    float *out2 = (L == 3) ? H2_save : E;  // where the second layer's output goes
+    const int w2 = (L == 3) ? M : D;
+    if (live && out2) {
+#pragma unroll
+        for (int ob = 0; ob < 2; ++ob)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int o = 32 * ob + 8 * q + 4 * h;
+                float *dst = out2 + (size_t)row * w2 + o;
+                if ((w2 & 3) == 0 && o + 3 < w2) {
+                    *(float4 *)dst = make_float4(z[ob][4 * q], z[ob][4 * q + 1], z[ob][4 * q + 2], z[ob][4 * q + 3]);
+                } else {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        if (o + r < w2) dst[r] = z[ob][4 * q + r];
+                }
+            }
+    }
+    if constexpr (L == 3) {
+        v16f a3 = (v16f){};
+#pragma unroll
+        for (int ob = 0; ob < 2; ++ob)
+#pragma unroll
+            for (int p = 0; p < 2; ++p) {
+                float x[8];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    x[e] = z[ob][8 * p + e];           // o = 32 ob + 16 p + 4 h + e
+                    x[4 + e] = z[ob][8 * p + 4 + e];   // o = 32 ob + 16 p + 8 + 4 h + e
+                }
+                if (PR) {                              // Z2 -> H2
+                    const int ob0 = 32 * ob + 16 * p + 4 * h;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        x[e] = x[e] > 0.f ? x[e] : S2s[ob0 + e] * x[e];
+                        x[4 + e] = x[4 + e] > 0.f ? x[4 + e] : S2s[ob0 + 8 + e] * x[4 + e];
+                    }
+                }
+                uint4 hi, lo;
+                split8(x, hi, lo);
+                const uint16_t *wr = &W3s[r32 * kW3S + 32 * ob + 16 * p + 4 * h];
+                const uint2 w0 = *(const uint2 *)wr, w1 = *(const uint2 *)(wr + 8);
+                const uint4 wv = make_uint4(w0.x, w0.y, w1.x, w1.y);
+                a3 = mfma_bf16(wv, hi, a3);
+                a3 = mfma_bf16(wv, lo, a3);
+            }
+        if (live) {
+            // runs of four outputs d = 8 q + 4 h + r; one store each where E's rows allow
+            const bool vec = (D & 3) == 0 && ((uintptr_t)E & 15) == 0;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int d = 8 * q + 4 * h;
+                const float4 c = *(const float4 *)&B3s[d];
+                float v[4] = {a3[4 * q] + c.x, a3[4 * q + 1] + c.y, a3[4 * q + 2] + c.z, a3[4 * q + 3] + c.w};
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    if (final_relu) v[r] = fmaxf(v[r], 0.f);
+                float *dst = E + (size_t)row * D + d;
+                if (vec) {
+                    if (d < D) *(float4 *)dst = make_float4(v[0], v[1], v[2], v[3]);
+                } else {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        if (d + r < D) dst[r] = v[r];
+                }
+            }
+        }
+    }
+}
+
 // PR: PReLU between the layers with per-channel slopes s1 [H] and s2 [M]
 // (3 layers).  H1b / H1lo then hold Z1 (split tiles: stored here) and the
 // layer-2 operand is the fp32 activation re-split into hi / lo; H2_save holds
@@ -1638,6 +1752,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
     __shared__ __attribute__((aligned(16))) uint16_t W3s[32 * kW3S];
     __shared__ __attribute__((aligned(16))) float S1s[PR ? H : 4];      // layer 1's slopes
     __shared__ float S2s[PR ? kMaxH2 : 1];                               // layer 2's slopes (3 layers)
+    __shared__ __attribute__((aligned(16))) float B3s[32];
     const int t = threadIdx.x, lane = ams_lane(), wave = t / AMS_WAVE;
     const int h = lane >> 5, r32 = lane & 31;
     const int Mo = (L == 3) ? M : D;           // width of the second layer's output
@@ -1678,6 +1793,10 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
             const int e = t + i * kThreads;
             if (e < 32 * kW3S) W3s[e] = v[i];
         }
+    }
+    if (L == 3 && t < 32) {
+        const float v = b3[t < D ? t : 0];
+        B3s[t] = t < D ? v : 0.f;
     }
     if (PR) {
         for (int i = t; i < H; i += kThreads) S1s[i] = s1[i];
@@ -1749,152 +1868,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
                 }
             }
         }
-        float z[2][16];
-#pragma unroll
-        for (int ob = 0; ob < 2; ++ob)
-#pragma unroll
-            for (int j = 0; j < 16; ++j) {
-                const float v = acc[ob][j] + bias[ob][j];
-                z[ob][j] = relu2 ? fmaxf(v, 0.f) : v;
-            }
-        float *out2 = (L == 3) ? H2_save : E;  // where the second layer's output goes
-        const int w2 = (L == 3) ? M : D;
-        if (live && out2) {
-#pragma unroll
-            for (int ob = 0; ob < 2; ++ob)
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int o = 32 * ob + 8 * q + 4 * h;
-                    float *dst = out2 + (size_t)row * w2 + o;
-                    if ((w2 & 3) == 0 && o + 3 < w2) {
-                        *(float4 *)dst = make_float4(z[ob][4 * q], z[ob][4 * q + 1], z[ob][4 * q + 2], z[ob][4 * q + 3]);
-                    } else {
-#pragma unroll
-                        for (int r = 0; r < 4; ++r)
-                            if (o + r < w2) dst[r] = z[ob][4 * q + r];
-                    }
-                }
-        }
-        if constexpr (L == 3) {
-            v16f a3 = (v16f){};
-#pragma unroll
-            for (int ob = 0; ob < 2; ++ob)
-#pragma unroll
-                for (int p = 0; p < 2; ++p) {
-                    float x[8];
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        x[e] = z[ob][8 * p + e];           // o = 32 ob + 16 p + 4 h + e
-                        x[4 + e] = z[ob][8 * p + 4 + e];   // o = 32 ob + 16 p + 8 + 4 h + e
-                    }
-                    if (PR) {                              // Z2 -> H2
-                        const int ob0 = 32 * ob + 16 * p + 4 * h;
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) {
-                            x[e] = x[e] > 0.f ? x[e] : S2s[ob0 + e] * x[e];
-                            x[4 + e] = x[4 + e] > 0.f ? x[4 + e] : S2s[ob0 + 8 + e] * x[4 + e];
-                        }
-                    }
-                    uint4 hi, lo;
-                    split8(x, hi, lo);
-                    const uint16_t *wr = &W3s[r32 * kW3S + 32 * ob + 16 * p + 4 * h];
-                    const uint2 w0 = *(const uint2 *)wr, w1 = *(const uint2 *)(wr + 8);
-                    const uint4 wv = make_uint4(w0.x, w0.y, w1.x, w1.y);
-                    a3 = mfma_bf16(wv, hi, a3);
-                    a3 = mfma_bf16(wv, lo, a3);
-                }
-            if (live) {
-#pragma unroll
-                for (int j = 0; j < 16; ++j) {
-                    const int d = acc_row(j, lane);
-                    if (d < D) {
-                        float v = a3[j] + b3[d];
-                        if (final_relu) v = fmaxf(v, 0.f);
-                        E[(size_t)row * D + d] = v;
-                    }
-                }
-            }
-        }
-    }
-}
-
-// The rest of a chunk after layer 2's products (acc[ob][j]: row lane % 32,
-// output 32 ob + acc_row(j, lane)): Z2 + b2 and its activation, stored to
-// H2_save (3 layers; Z2 itself with PReLU) or E (2 layers), then for 3
-// layers E = H2 W3^T + b3 on MFMA with W3 rows in LDS (kW3S bf16 apart) and
-// H2 split into hi and lo parts straight from the registers.
-template <int L, bool PR>
-__device__ __forceinline__ void tfb_finish(const v16f (&acc)[2], const float (&bias)[2][16], bool relu2,
-                                           const uint16_t *W3s, const float *S2s, const float *__restrict__ b3,
-                                           int final_relu, int M, int D, int row, bool live,
-                                           float *__restrict__ H2_save, float *__restrict__ E, int lane)
-{
-    const int h = lane >> 5, r32 = lane & 31;
-    float z[2][16];
-#pragma unroll
-    for (int ob = 0; ob < 2; ++ob)
-#pragma unroll
-        for (int j = 0; j < 16; ++j) {
-            const float v = acc[ob][j] + bias[ob][j];
-            z[ob][j] = relu2 ? fmaxf(v, 0.f) : v;
-        }
-    float *out2 = (L == 3) ? H2_save : E;  // where the second layer's output goes
-    const int w2 = (L == 3) ? M : D;
-    if (live && out2) {
-#pragma unroll
-        for (int ob = 0; ob < 2; ++ob)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int o = 32 * ob + 8 * q + 4 * h;
-                float *dst = out2 + (size_t)row * w2 + o;
-                if ((w2 & 3) == 0 && o + 3 < w2) {
-                    *(float4 *)dst = make_float4(z[ob][4 * q], z[ob][4 * q + 1], z[ob][4 * q + 2], z[ob][4 * q + 3]);
-                } else {
-#pragma unroll
-                    for (int r = 0; r < 4; ++r)
-                        if (o + r < w2) dst[r] = z[ob][4 * q + r];
-                }
-            }
-    }
-    if constexpr (L == 3) {
-        v16f a3 = (v16f){};
-#pragma unroll
-        for (int ob = 0; ob < 2; ++ob)
-#pragma unroll
-            for (int p = 0; p < 2; ++p) {
-                float x[8];
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    x[e] = z[ob][8 * p + e];           // o = 32 ob + 16 p + 4 h + e
-                    x[4 + e] = z[ob][8 * p + 4 + e];   // o = 32 ob + 16 p + 8 + 4 h + e
-                }
-                if (PR) {                              // Z2 -> H2
-                    const int ob0 = 32 * ob + 16 * p + 4 * h;
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        x[e] = x[e] > 0.f ? x[e] : S2s[ob0 + e] * x[e];
-                        x[4 + e] = x[4 + e] > 0.f ? x[4 + e] : S2s[ob0 + 8 + e] * x[4 + e];
-                    }
-                }
-                uint4 hi, lo;
-                split8(x, hi, lo);
-                const uint16_t *wr = &W3s[r32 * kW3S + 32 * ob + 16 * p + 4 * h];
-                const uint2 w0 = *(const uint2 *)wr, w1 = *(const uint2 *)(wr + 8);
-                const uint4 wv = make_uint4(w0.x, w0.y, w1.x, w1.y);
-                a3 = mfma_bf16(wv, hi, a3);
-                a3 = mfma_bf16(wv, lo, a3);
-            }
-        if (live) {
-#pragma unroll
-            for (int j = 0; j < 16; ++j) {
-                const int d = acc_row(j, lane);
-                if (d < D) {
-                    float v = a3[j] + b3[d];
-                    if (final_relu) v = fmaxf(v, 0.f);
-                    E[(size_t)row * D + d] = v;
-                }
-            }
-        }
+        tfb_finish<L, PR>(acc, bias, relu2, W3s, S2s, B3s, final_relu, M, D, row, live, H2_save, E, lane);
     }
 }
 
@@ -1923,7 +1897,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
     __shared__ __attribute__((aligned(16))) uint16_t W3s[32 * kW3S];
     __shared__ __attribute__((aligned(16))) float B1s[kMaxH1];
     __shared__ __attribute__((aligned(16))) float S1s[PR ? kMaxH1 : 4];
-    __shared__ float S2s[PR ? kMaxH2 : 1];
+    __shared__ float S2s[PR ? kMaxH2 : 1], B2s[kMaxH2];
+    __shared__ __attribute__((aligned(16))) float B3s[32];
     const int t = threadIdx.x, lane = ams_lane(), q = t / AMS_WAVE;
     const int h = lane >> 5, r32 = lane & 31;
     const int Mo = (L == 3) ? M : D;
@@ -1944,27 +1919,34 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
 #pragma unroll
         for (int ob = 0; ob < 2; ++ob)
             if (32 * ob + r32 >= Mo) aw[s4][ob] = make_uint4(0, 0, 0, 0);
-    if (L == 3)
-        for (int e = t; e < 32 * kW3S; e += kThreads) {
-            const int d = e / kW3S, o = e % kW3S;
-            W3s[e] = (d < D && o < M) ? W3[d * M + o] : (uint16_t)0;
+    // W3, the biases and the slopes: every load unconditional (an index past the
+    // end reads element 0 and is dropped), so all are in flight together
+    static_assert(kThreads == H && kMaxH2 <= kThreads, "one element per thread");
+    constexpr int n3 = (32 * kW3S + kThreads - 1) / kThreads;
+    uint16_t w3v[L == 3 ? n3 : 1];
+    if constexpr (L == 3) {
+#pragma unroll
+        for (int i = 0; i < n3; ++i) {
+            const int e = t + i * kThreads, d = e / kW3S, o = e % kW3S;
+            const bool ok = e < 32 * kW3S && d < D && o < M;
+            const uint16_t x = W3[ok ? d * M + o : 0];
+            w3v[i] = ok ? x : (uint16_t)0;
         }
-    for (int i = t; i < H; i += kThreads) B1s[i] = b1[i];
-    if (PR) {
-        for (int i = t; i < H; i += kThreads) S1s[i] = s1[i];
-        if (L == 3)
-            for (int i = t; i < kMaxH2; i += kThreads) S2s[i] = i < M ? s2[i] : 0.f;
     }
-    // wave 0's layer-2 biases (output 32 ob + acc_row(j, lane))
-    float bias[2][16];
+    const float b1v = b1[t], b2v = b2[t < Mo ? t : 0], b3v = L == 3 ? b3[t < D ? t : 0] : 0.f;
+    const float s1v = PR ? s1[t] : 0.f, s2v = PR && L == 3 ? s2[t < M ? t : 0] : 0.f;
+    if constexpr (L == 3) {
 #pragma unroll
-    for (int ob = 0; ob < 2; ++ob)
-#pragma unroll
-        for (int j = 0; j < 16; ++j) {
-            const int o = 32 * ob + acc_row(j, lane);
-            const float bv = b2[o < Mo ? o : 0];
-            bias[ob][j] = o < Mo ? bv : 0.f;
+        for (int i = 0; i < n3; ++i) {
+            const int e = t + i * kThreads;
+            if (e < 32 * kW3S) W3s[e] = w3v[i];
         }
+    }
+    B1s[t] = b1v;
+    if (t < kMaxH2) B2s[t] = t < Mo ? b2v : 0.f;
+    if (L == 3 && t < 32) B3s[t] = t < D ? b3v : 0.f;
+    if (PR) S1s[t] = s1v;
+    if (PR && L == 3 && t < kMaxH2) S2s[t] = t < M ? s2v : 0.f;
     __syncthreads();
 
     const bool relu2 = (L == 3 && !PR) || (L == 2 && final_relu);
@@ -2074,7 +2056,12 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
 #pragma unroll
                 for (int j = 0; j < 16; ++j)
                     z[ob][j] = ((Zq[0][ob][j][lane] + Zq[1][ob][j][lane]) + Zq[2][ob][j][lane]) + Zq[3][ob][j][lane];
-            tfb_finish<L, PR>(z, bias, relu2, W3s, S2s, b3, final_relu, M, D, row, live, H2_save, E, lane);
+            float bias[2][16];                  // output 32 ob + acc_row(j, lane)
+#pragma unroll
+            for (int ob = 0; ob < 2; ++ob)
+#pragma unroll
+                for (int j = 0; j < 16; ++j) bias[ob][j] = B2s[32 * ob + acc_row(j, lane)];
+            tfb_finish<L, PR>(z, bias, relu2, W3s, S2s, B3s, final_relu, M, D, row, live, H2_save, E, lane);
         }
         __syncthreads();                        // Zq is free for the next chunk
     }

@@ -146,3 +146,30 @@ def test_split_weight_gradient(dims, n, prelu):
                 assert_close(ds[l], rs[l], RTOL[dtype], f"{dtype} dslope{l + 1}")
         err[dtype] = float((dW[0].double() - rW[0]).norm() / rW[0].norm().clamp_min(1e-30))
     assert err["f32x3"] <= max(err["f32"], 1.5e-7), err     # (2^-23: a sum of a few products)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("cap", [300, 131072])      # tails after the stream-K and the row-split layer
+@pytest.mark.parametrize("M,D", [(64, 12), (64, 10), (63, 32), (17, 4), (33, 1), (16, 29)])
+def test_tail_output_widths(M, D, cap, dtype):
+    """The last layer's widths and a middle layer that is no multiple of its
+    blocks of 16, with E's rows on 16-byte boundaries and 4 bytes past them."""
+    dims, n = (4096, 256, M, D), 261
+    print(f"tail widths {dims} cap={cap} {dtype}", flush=True)
+    T, W, b, uniq, dE = model(dims, dtype, n)
+    mlp = ams.make_mlp(dims, dtype)
+    n_uniq = torch.full((1,), n, dtype=torch.int32, device="cuda")
+    ids = torch.full((cap,), -1, dtype=torch.int32, device="cuda")
+    ids[:n] = uniq
+    H1 = torch.empty((cap, 256), dtype=torch.bfloat16 if dtype == "bf16" else torch.float32, device="cuda")
+    H2 = torch.empty((cap, M), device="cuda")
+    ws = torch.empty(ams.ams_embed_workspace(mlp, cap), dtype=torch.uint8, device="cuda")
+    h, _, _ = reference(T, W, b, uniq, dE, torch.zeros((n, 256), device="cuda"), torch.zeros((n, M), device="cuda"))
+    for shift in (0, 1):
+        buf = torch.full((cap * D + 1,), float("nan"), device="cuda")
+        E = buf[shift:shift + cap * D].view(cap, D)
+        ams.ams_embed_fwd(mlp, T, ids, n_uniq, cap, W, b, H1, H2, E, ws)
+        torch.cuda.synchronize()
+        assert_close(H2[:n], h[2], 1e-4, "H2")
+        assert_close(E[:n], h[3], 1e-4, f"E shift={shift}", rows=True)
+        assert bool(buf[shift + n * D:].isnan().all())
