@@ -345,28 +345,56 @@ __device__ __forceinline__ void net_fwd_load(const float *__restrict__ W, int K,
     }
 }
 
+// The four lanes of a column (l, l + 16, l + 32, l + 48) as a 4 x 4 matrix of
+// their four elements, transposed: element j of lane quarter q was element q of
+// quarter j.  A quad read per lane so becomes the operands of four steps whose
+// k are four consecutive ones.
+__device__ __forceinline__ f4 quarters_transposed(f4 v)
+{
+    typedef unsigned u2 __attribute__((ext_vector_type(2)));
+    const u2 a = __builtin_amdgcn_permlane32_swap(__float_as_uint(v[0]), __float_as_uint(v[2]), false, false);
+    const u2 b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v[1]), __float_as_uint(v[3]), false, false);
+    const u2 c = __builtin_amdgcn_permlane16_swap(a[0], b[0], false, false);
+    const u2 d = __builtin_amdgcn_permlane16_swap(a[1], b[1], false, false);
+    return (f4){__uint_as_float(c[0]), __uint_as_float(c[1]), __uint_as_float(d[0]), __uint_as_float(d[1])};
+}
+
+// Width of the parts that a forward sum is added up in: each part's terms in
+// the order of k, the parts in order onto the bias.  A unit whose sum is within
+// rounding of zero takes the side that this order gives it, so the order is
+// part of the results: it is that of 512 threads that share a layer's outputs
+// and, for narrow layers, its K in quads.
+__device__ __forceinline__ int net_fwd_part(int K, int O)
+{
+    int P = 512 / O;
+    if (P < 1) P = 1;
+    if (P > (K + 15) / 16) P = (K + 15) / 16;
+    return (((K + P - 1) / P) + 3) & ~3;
+}
+
 // out[s][o] = act(b[o] + sum_k in[s][k] W[o][k]): output tile ot (w: its
-// first operands, afterwards those of tile next); the result's rows are outputs, so a lane holds four
-// consecutive outputs of one sample.  With PReLU the pre-activations go to
-// zout.
+// first operands, afterwards those of tile next); the result's rows are
+// outputs, so a lane holds four consecutive outputs of one sample.  An MFMA
+// adds its four products in the order of k, each with a rounding of its own
+// (as four fused multiply-adds), so one chain of them is net_fwd_part's order;
+// the matrix core is busy as long as the chain waits, so more chains would not
+// be faster.  With PReLU the pre-activations go to zout.
 __device__ __forceinline__ void net_fwd_tile(const float *in, int ldi, int K, float *out, float *zout, int ldo, int O,
                                              int ot, int next, f4 (&w)[kFwdBatch], const float *__restrict__ W,
                                              const float *__restrict__ bias, bool hidden,
                                              const float *__restrict__ slope)
 {
     const int lane = ams_lane(), s = lane & 15, q = lane >> 4, o0 = 16 * ot + 4 * q, groups = (K + 15) / 16;
-    float b[4], sl[4];
+    const int part = net_fwd_part(K, O);
+    f4 v, acc = (f4){0.f, 0.f, 0.f, 0.f};
+    float sl[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-        b[e] = bias[min(o0 + e, O - 1)];
+        v[e] = bias[min(o0 + e, O - 1)];
         sl[e] = slope ? slope[min(o0 + e, O - 1)] : 0.f;
     }
-    // four chains, added at the end: no MFMA waits for the one before it, and
-    // a sum's rounding grows with a quarter of its terms
-    f4 acc[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) acc[e] = (f4){0.f, 0.f, 0.f, 0.f};
     const float *x0 = in + s * ldi;
+    int end = part;
 #pragma unroll 1
     for (int g = 0; g < groups; g += kFwdBatch) {
         f4 nx[kFwdBatch];
@@ -377,17 +405,30 @@ __device__ __forceinline__ void net_fwd_tile(const float *in, int ldi, int K, fl
         for (int i = 0; i < kFwdBatch; ++i) x[i] = net_quad(x0, 16 * (g + i) + 4 * q, K);
 #pragma unroll
         for (int i = 0; i < kFwdBatch; ++i) {
-            if (g + i >= groups) break;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) acc[e] = mfma4(w[i][e], x[i][e], acc[e]);
+            x[i] = quarters_transposed(x[i]);
+            w[i] = quarters_transposed(w[i]);
         }
+#pragma unroll
+        for (int i = 0; i < kFwdBatch; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int k = 16 * (g + i) + 4 * j;
+                if (k >= K) break;
+                if (k == end) {
+                    v += acc;
+                    acc = (f4){0.f, 0.f, 0.f, 0.f};
+                    end += part;
+                }
+                acc = mfma4(w[i][j], x[i][j], acc);
+            }
 #pragma unroll
         for (int i = 0; i < kFwdBatch; ++i) w[i] = nx[i];
     }
+    v += acc;
     f4 z, y;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-        z[e] = o0 + e < O ? ((acc[0][e] + acc[1][e]) + (acc[2][e] + acc[3][e])) + b[e] : 0.f;
+        z[e] = o0 + e < O ? v[e] : 0.f;
         y[e] = hidden ? ctr_act(z[e], slope, sl[e]) : z[e];
     }
     if (o0 < O) {
