@@ -154,9 +154,9 @@ __host__ __device__ inline int net_part_size(const CtrArgs &a)
 // What bounds these kernels: a dozen dependent phases of a barrier, an L2 round
 // trip and a few tens of MFMAs per wave (counters on the 72-200-80-2 net: a
 // wave waits half of its time and issues a third of it), and last the partial
-// rows' stores (31 MB at 4096 samples, 8 us).  4096 samples with PReLU, kernel
-// trace: that net 55 us with the layers as vector FMA loops, 41 us so; a pair
-// of 48-64-32 towers 57 and 27 us (side by side, four waves each).
+// rows' stores (31 MB at 4096 samples, 8 us).  4096 samples with PReLU, whole
+// call: that net 60.8 us with the layers as vector FMA loops, 56.8 us so; a
+// pair of 48-64-32 towers 62.3 and 33.4 us (side by side, four waves each).
 typedef float f4 __attribute__((ext_vector_type(4)));
 typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));   // any float address
 
@@ -376,9 +376,11 @@ __device__ __forceinline__ int net_fwd_part(int K, int O)
 // first operands, afterwards those of tile next); the result's rows are
 // outputs, so a lane holds four consecutive outputs of one sample.  An MFMA
 // adds its four products in the order of k, each with a rounding of its own
-// (as four fused multiply-adds), so one chain of them is net_fwd_part's order;
-// the matrix core is busy as long as the chain waits, so more chains would not
-// be faster.  With PReLU the pre-activations go to zout.
+// (as four fused multiply-adds), so one chain of them is net_fwd_part's order.
+// The calls measured above with other forwards: four interleaved chains, in an
+// order of their own, 47.4 and 30.4 us; operands by 4-byte reads 67.8 and 37.8;
+// batches that follow the parts, with no test per step, 59.1 and 36.8.  With
+// PReLU the pre-activations go to zout.
 __device__ __forceinline__ void net_fwd_tile(const float *in, int ldi, int K, float *out, float *zout, int ldo, int O,
                                              int ot, int next, f4 (&w)[kFwdBatch], const float *__restrict__ W,
                                              const float *__restrict__ bias, bool hidden,
