@@ -70,8 +70,11 @@ __device__ __forceinline__ void st_relaxed(uint32_t *p, uint32_t v)
 // block (one digit each) read consecutive words.  lookback_publish has
 // published the aggregate (tile 0: the prefix); the inclusive prefix is
 // published here.  Every tile publishes before it waits, so
-// each wait ends; the wait is nevertheless bounded (kSpinLimit re-reads), and
-// a bound that is hit is recorded in *err instead of spinning on.
+// each wait ends; the wait is nevertheless bounded (`limit` re-reads), and a
+// bound that is hit is recorded in *err instead of spinning on.  What follows
+// such a give-up is wrong but stays in bounds: the passes drop positions past
+// the buffers, and dd_unique clamps the occurrences that it uses as indexes
+// (positions that nothing was written to hold whatever the workspace held).
 constexpr int kSpinLimit = 1 << 22;
 
 __device__ __forceinline__ void lookback_publish(uint32_t *words, int stride, int t, uint32_t count)
@@ -79,7 +82,7 @@ __device__ __forceinline__ void lookback_publish(uint32_t *words, int stride, in
     st_relaxed(&words[(size_t)t * stride], (t == 0 ? kPrefix : kAgg) | count);
 }
 
-__device__ uint32_t lookback(uint32_t *words, int stride, int t, uint32_t count, int32_t *err)
+__device__ uint32_t lookback(uint32_t *words, int stride, int t, uint32_t count, int limit, int32_t *err)
 {
     if (t == 0) return 0;
     // walk back in batches of independent reads (one round trip each); the
@@ -99,7 +102,7 @@ __device__ uint32_t lookback(uint32_t *words, int stride, int t, uint32_t count,
             ready &= (w[i] & ~kValMask) != 0;
         }
         if (!ready) {                             // some tile of the batch has not published
-            if (++spins < kSpinLimit) continue;
+            if (++spins < limit) continue;
             __hip_atomic_store(err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             break;
         }
@@ -121,7 +124,7 @@ __device__ uint32_t lookback(uint32_t *words, int stride, int t, uint32_t count,
 // The same look-back walked by one whole wave: lane i reads the word of tile
 // (hi - i), so 64 earlier tiles cost one round trip.  The lowest lane holding
 // an inclusive prefix is the nearest one; the sum runs up to it.
-__device__ uint32_t lookback_wave(uint32_t *words, int t, uint32_t count, bool &hit)
+__device__ uint32_t lookback_wave(uint32_t *words, int t, uint32_t count, int limit, bool &hit)
 {
     const int lane = ams_lane();
     if (t == 0) {
@@ -135,7 +138,7 @@ __device__ uint32_t lookback_wave(uint32_t *words, int t, uint32_t count, bool &
         const int j = hi - lane;
         const uint32_t w = j >= 0 ? ld_relaxed(&words[j]) : kPrefix;   // before tile 0: prefix 0
         if (ams_ballot((w & ~kValMask) == 0) != 0) {                   // not all published yet
-            if (++spins < kSpinLimit) continue;
+            if (++spins < limit) continue;
             hit = true;
             break;
         }
@@ -153,6 +156,7 @@ __device__ uint32_t lookback_wave(uint32_t *words, int t, uint32_t count, bool &
 
 struct Plan {
     int bits, passes, width, ntiles;
+    int limit;                                 // re-reads of a bounded wait (kSpinLimit)
 };
 
 __device__ __forceinline__ int pass_bits(const Plan &P, int pass)
@@ -470,7 +474,7 @@ __global__ __launch_bounds__(kThreads) void dd_pass(const uint32_t *__restrict__
             vs[pos] = val[r];
         }
     uint32_t before = 0;
-    if (t < (1 << bits)) before = lookback(lb, R, blockIdx.x, (uint32_t)tile_cnt, err);
+    if (t < (1 << bits)) before = lookback(lb, R, blockIdx.x, (uint32_t)tile_cnt, P.limit, err);
     gofs[t] = gbase + (int)before - tstart;
     __syncthreads();
     const int m = min(TILE, n - tile0);
@@ -480,8 +484,8 @@ __global__ __launch_bounds__(kThreads) void dd_pass(const uint32_t *__restrict__
         if (i < m) {
             const uint32_t k = ks[i];
             const int pos = gofs[(k >> shift) & mask] + i;
-            // (a bounded wait that gave up leaves a wrong offset: the status
-            // says so, and nothing is written outside the buffers)
+            // (a bounded wait that gave up leaves a wrong offset, here or in a
+            // pass before: the status says so, and this store stays inside)
             if ((unsigned)pos < (unsigned)n) {
                 kout[pos] = k;
                 vout[pos] = vs[i];
@@ -514,7 +518,8 @@ constexpr int kBucketStride = 16;              // counters 64 bytes apart
 template <int THREADS, bool BUCKET>
 __global__ __launch_bounds__(THREADS) void dd_unique(const uint32_t *__restrict__ k,
                                                       const int32_t *__restrict__ v, int n,
-                                                      uint32_t *__restrict__ words, const int32_t *__restrict__ err,
+                                                      uint32_t *__restrict__ words, int limit,
+                                                      const int32_t *__restrict__ err,
                                                       unsigned long long *__restrict__ done,
                                                       const int32_t *__restrict__ bad, int n_prep,
                                                       int32_t *__restrict__ uniq, int32_t *__restrict__ inv,
@@ -550,6 +555,10 @@ __global__ __launch_bounds__(THREADS) void dd_unique(const uint32_t *__restrict_
             vv[q] = i0 + q < n ? v[i0 + q] : 0;
         }
     }
+    // an index from here on (inv, the buckets, and through occ_perm the pooling
+    // backward's records): inside the batch also where a pass gave up a wait
+#pragma unroll
+    for (int q = 0; q < kItems; ++q) vv[q] = (int32_t)min((uint32_t)vv[q], (uint32_t)(n - 1));
     const uint32_t kprev = (i0 > 0 && i0 < n) ? k[i0 - 1] : 0u;
     if (BUCKET)
         for (int i = t; i < kMaxBuckets; i += THREADS) bcnt[i] = 0;
@@ -569,7 +578,7 @@ __global__ __launch_bounds__(THREADS) void dd_unique(const uint32_t *__restrict_
     if (w == 0) {
         int tot = 0;
         for (int x = 0; x < WAVES; ++x) tot += ws[x];
-        const uint32_t b = lookback_wave(words, blockIdx.x, (uint32_t)tot, hit);
+        const uint32_t b = lookback_wave(words, blockIdx.x, (uint32_t)tot, limit, hit);
         if (t == 0) tile_base = b;
     }
     __syncthreads();
@@ -721,6 +730,7 @@ constexpr Layout layout(int64_t n_occ, int32_t n_ids)
     L.P.bits = id_bits(n_ids);
     L.P.passes = (L.P.bits + kMaxBits - 1) / kMaxBits;
     L.P.width = (L.P.bits + L.P.passes - 1) / L.P.passes;
+    L.P.limit = kSpinLimit;
     L.utiles = (int)((n_occ + kTile - 1) / kTile);
     L.wide = n_occ >= kWideOcc;
     L.bucket = n_occ >= kBucketOcc && n_occ <= (int64_t)kMaxBuckets << kBucketBits;
@@ -831,12 +841,12 @@ ams_status dedup_enqueue(const int32_t *ids, int n, int32_t n_ids, int32_t *uniq
         int32_t *po = (int32_t *)bufk[L.P.passes & 1], *pr = bufv[L.P.passes & 1];
         const int tiles = (n + 8 * kInvThreads - 1) / (8 * kInvThreads);
         AMS_LAUNCH("dd_unique", st, (dd_unique<kInvThreads, true><<<tiles, kInvThreads, 0, st>>>(
-                                        kin, vin, n, uw, err, done, bad, n_prep, uniq, inv, occ_perm, uniq_off, n_uniq,
+                                        kin, vin, n, uw, L.P.limit, err, done, bad, n_prep, uniq, inv, occ_perm, uniq_off, n_uniq,
                                         dev_status, hpart + kMaxPasses * kRadix, po, pr)));
         AMS_LAUNCH("dd_inverse", st, dd_inverse<<<((n - 1) >> kBucketBits) + 1, kInvThreads, 0, st>>>(po, pr, n, inv));
     } else {
         AMS_LAUNCH("dd_unique", st, (dd_unique<kThreads, false><<<L.utiles, kThreads, 0, st>>>(
-                                        kin, vin, n, uw, err, done, bad, n_prep, uniq, inv, occ_perm, uniq_off, n_uniq,
+                                        kin, vin, n, uw, L.P.limit, err, done, bad, n_prep, uniq, inv, occ_perm, uniq_off, n_uniq,
                                         dev_status, nullptr, nullptr, nullptr)));
     }
     return ams_launch_status();
@@ -879,18 +889,43 @@ extern "C" size_t ams_dedup_workspace(int64_t n_occ, int32_t n_ids)
     return workspace_bound(n_occ, n_ids);
 }
 
+namespace {
+
+ams_status dedup_limited(const int32_t *ids, int64_t n_occ, int32_t n_ids, int32_t *uniq, int32_t *inv,
+                         int32_t *occ_perm, int32_t *uniq_off, int32_t *n_uniq, int32_t *dev_status, void *ws,
+                         size_t ws_bytes, int limit, void *stream)
+{
+    if (n_occ < 0 || n_occ > kMaxOcc || n_ids < 1) return AMS_ERR_SIZE;
+    if (!uniq_off || !n_uniq || !dev_status) return AMS_ERR_NULL;
+    if (n_occ > 0 && (!ids || !uniq || !inv || !occ_perm || !ws)) return AMS_ERR_NULL;
+    Layout L = layout(n_occ, n_ids);
+    if (n_occ > 0 && ws_bytes < L.total) return AMS_ERR_WORKSPACE;
+    L.P.limit = limit;
+    return dedup_enqueue(ids, (int)n_occ, n_ids, uniq, inv, occ_perm, uniq_off, n_uniq, dev_status, (char *)ws, L,
+                         (hipStream_t)stream);
+}
+
+}  // namespace
+
 extern "C" ams_status ams_dedup(const int32_t *ids, int64_t n_occ, int32_t n_ids, int32_t *uniq,
                                 int32_t *inv, int32_t *occ_perm, int32_t *uniq_off,
                                 int32_t *n_uniq, int32_t *dev_status, void *ws, size_t ws_bytes,
                                 void *stream)
 {
-    if (n_occ < 0 || n_occ > kMaxOcc || n_ids < 1) return AMS_ERR_SIZE;
-    if (!uniq_off || !n_uniq || !dev_status) return AMS_ERR_NULL;
-    if (n_occ > 0 && (!ids || !uniq || !inv || !occ_perm || !ws)) return AMS_ERR_NULL;
-    const Layout L = layout(n_occ, n_ids);
-    if (n_occ > 0 && ws_bytes < L.total) return AMS_ERR_WORKSPACE;
-    return dedup_enqueue(ids, (int)n_occ, n_ids, uniq, inv, occ_perm, uniq_off, n_uniq, dev_status, (char *)ws, L,
-                         (hipStream_t)stream);
+    return dedup_limited(ids, n_occ, n_ids, uniq, inv, occ_perm, uniq_off, n_uniq, dev_status, ws, ws_bytes, kSpinLimit,
+                         stream);
+}
+
+// ams_dedup with the waits bounded at `limit` re-reads: not part of the
+// interface (the header does not declare it).  With a limit of 1 a tile gives
+// up as soon as an earlier one is not ready, which is how the tests reach what
+// follows a give-up.
+extern "C" ams_status amsi_dedup_limit(const int32_t *ids, int64_t n_occ, int32_t n_ids, int32_t *uniq, int32_t *inv,
+                                       int32_t *occ_perm, int32_t *uniq_off, int32_t *n_uniq, int32_t *dev_status,
+                                       void *ws, size_t ws_bytes, int32_t limit, void *stream)
+{
+    return dedup_limited(ids, n_occ, n_ids, uniq, inv, occ_perm, uniq_off, n_uniq, dev_status, ws, ws_bytes, limit,
+                         stream);
 }
 
 extern "C" ams_status ams_dedup_noalloc(const int32_t *ids, int64_t n_occ, int32_t n_ids, int32_t *uniq,

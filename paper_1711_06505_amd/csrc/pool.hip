@@ -555,14 +555,14 @@ __global__ __launch_bounds__(kThreads) void pool_bwd_seg(int D, int n_occ, int c
         }
     }
     // level 3: the rows each position's gradient is made of.  An occurrence
-    // whose unique index is at or past the caller's capacity (possible only
-    // when the capacity is below the real unique count) is dropped: its row of
-    // dE does not exist.
+    // whose unique index is not below cap is dropped: its row of dE does not
+    // exist (a capacity below the real unique count, or the inverse index of a
+    // dedup that reported an internal failure, where it may also be negative).
     float r[CAT ? CPW : 1][DM];  // concat: the behavior's slice of dU, or the ad's dA
     if constexpr (CAT) {
 #pragma unroll
         for (int c = 0; c < CPW; ++c) {
-            const bool valid = uk[c] < cap;
+            const bool valid = (unsigned)uk[c] < (unsigned)cap;
             const int i = si[c] >= 0 ? si[c] : -1 - si[c];
 #pragma unroll
             for (int d = 0; d < DM; ++d) r[c][d] = 0.f;
@@ -575,7 +575,7 @@ __global__ __launch_bounds__(kThreads) void pool_bwd_seg(int D, int n_occ, int c
     } else {
 #pragma unroll
         for (int c = 0; c < CPW; ++c)
-            stage_rows<P::lpr>(pack, uk[c] < cap && si[c] != -1 ? (unsigned)si[c] : 0u,
+            stage_rows<P::lpr>(pack, (unsigned)uk[c] < (unsigned)cap && si[c] != -1 ? (unsigned)si[c] : 0u,
                                rows + c * AMS_WAVE * P::row, lane);
         staged();
     }
@@ -585,7 +585,7 @@ __global__ __launch_bounds__(kThreads) void pool_bwd_seg(int D, int n_occ, int c
         const int ch = chv[c];
         if (ch < 0) break;
         const int c0 = ch * AMS_WAVE, c1 = c0 + AMS_WAVE;
-        const bool valid = uk[c] < cap;
+        const bool valid = (unsigned)uk[c] < (unsigned)cap;
         int u = valid ? uk[c] : -1 - lane;       // distinct per invalid lane: never joins a run
         float v[DM];
         if constexpr (CAT) {
@@ -716,6 +716,12 @@ constexpr int kSmallChunks = 16384;
 // kernel a run of at most fix_short head chunks is summed by one lane in the
 // butterfly's association, (h0 + h2) + (h1 + h3), so which kernel or path
 // takes a run changes nothing in its sum.
+__device__ __forceinline__ int fix_last(const int32_t *__restrict__ uniq_off, int u, int ch, int nch)
+{
+    // (within the chunks also for the offsets of a dedup that reported a failure)
+    return max(ch, min((uniq_off[u + 1] - 1) / AMS_WAVE, nch - 1));
+}
+
 template <int DM>
 __device__ __forceinline__ void fix_one_lane(int D, bool full, int ch, int u, int last,
                                              const float *__restrict__ head_part,
@@ -795,7 +801,7 @@ __global__ __launch_bounds__(kThreads) void pool_bwd_fix(int D, int nch, bool fu
     if (ch >= nch) return;
     const int u = cross[ch];
     if (u < 0) return;
-    const int last = (uniq_off[u + 1] - 1) / AMS_WAVE;
+    const int last = fix_last(uniq_off, u, ch, nch);
     fix_one_wave<DM>(D, full, ch, u, last, head_part, tail_part, bsum, dE, accumulate);
 }
 
@@ -815,7 +821,7 @@ __global__ __launch_bounds__(kThreads) void pool_bwd_fix64(int D, int nch, bool 
     const int lane = ams_lane(), wave = threadIdx.x / AMS_WAVE;
     const int ch = (blockIdx.x * kWaves + wave) * AMS_WAVE + lane;
     const int u = ch < nch ? cross[ch] : -1;
-    const int last = u >= 0 ? (uniq_off[u + 1] - 1) / AMS_WAVE : ch;
+    const int last = u >= 0 ? fix_last(uniq_off, u, ch, nch) : ch;
     const bool is_long = u >= 0 && last - ch > fix_short<DM>();
     if (u >= 0 && !is_long) fix_one_lane<DM>(D, full, ch, u, last, head_part, tail_part, dE, accumulate);
     const uint64_t todo = __ballot(is_long);
@@ -896,7 +902,7 @@ void launch_bwd(int B, int D, const int32_t *seg_off, int64_t n_beh, const int32
 #define SEG_LAUNCH(CPWV)                                                                                     \
     AMS_LAUNCH("pool_bwd_seg", st, (pool_bwd_seg<MODE, DM, CPWV><<<(p.nch + kWaves * CPWV - 1) / (kWaves * CPWV), \
                                                                   kThreads, 0, st>>>(                        \
-                                       D, n_occ, cap, occ_perm, uniq_off, dU, dA, rec, pack, p.nch, dE, head, tail, \
+                                       D, n_occ, min(cap, n_occ), occ_perm, uniq_off, dU, dA, rec, pack, p.nch, dE, head, tail, \
                                        cross, accumulate, seg_off, Lc)))
     if (small) SEG_LAUNCH(1);
     else SEG_LAUNCH((seg_cpw<MODE, DM>()));
