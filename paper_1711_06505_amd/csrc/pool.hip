@@ -321,11 +321,12 @@ __global__ __launch_bounds__(kThreads) void pool_concat_fwd_k(int B, int D, int 
 }
 
 // The record of occurrence k, written in occurrence order for the stable-order
-// pass to read with one access: its unique index and the packed row its
-// gradient is made of (i for a behavior of sample i, B + i for its ad, -1 for
-// none); with attention also the factors of the row's two halves (float bits):
-// the behavior's weight w_j and score gradient ds_j, 1 and 1 for an ad.  The
-// concatenate aggregator has no packed rows: i, or -1 - i for the ad.
+// pass to read with one access: its unique index and where the one or two rows
+// lie that its gradient is made of; with attention also the factors of the two
+// rows (float bits): the behavior's weight w_j and score gradient ds_j, 1 and 1
+// for an ad.  With packed rows (PACK, use_packed) the second word is the packed
+// row: i for a behavior of sample i, B + i for its ad, -1 for none.  Else the
+// rows are read where they are: i, or -1 - i for the ad.
 template <int MODE>
 constexpr bool wide_rec() { return MODE == AMS_POOL_ATT || MODE == kPoolQuery; }
 
@@ -341,11 +342,56 @@ struct Pack {
     static constexpr int lpr = row / 4;                                 // lanes (16-byte pieces) per row
 };
 
-// (1) per sample: the records of its occurrences and its packed rows; attention
-// terms c_i = g_i . u_i and da_i = sum_j ds_j e_j, ds_j = w_j (g_i . e_j - c_i)
-// (da: the query's gradient in the query mode).  An ad's upstream gradient is
-// dA_i + dA2_i where both are given.
+// Packed rows, or each row where it is.  Packing costs the per-sample pass two
+// rows' stores (50,000 samples: 5 us of 15), and a packed row has the bytes of
+// the widest D of its kind.  It saves the stable-order pass lines and loads per
+// position, which counts where the rows are wide or not whole 16-byte pieces,
+// the lists long enough for every row to be read some ten times, and the batch
+// beyond what the launches themselves cost.  pieces: the loads a position takes
+// where the rows are, against the P::lpr 16-byte pieces of a packed row (max has
+// its argmax positions to load one by one as well).  The backward in us with
+// each row where it is / packed, samples x mean list length:
+//   sum        D=4 16384x183 85/80, 65536x183 264/310 (rows of 16 bytes stay in
+//              the L2); D=8 16384x183 89/81, 65536x183 296/315; D=10 20000x10
+//              27/29, 65536x10 57/52; D=12 50000x1 22/28, 16384x60 46/46,
+//              65536x60 134/126; D=16 16384x60 55/52, 20000x10 28/30
+//   max        D=4 65536x60 119/140; D=8 20000x10 26/30, 4096x183 41/39; D=12
+//              50000x1 25/29, 20000x30 48/40, 65536x183 485/362; D=20 8192x15
+//              30/33, 4096x60 41/40
+//   attention  (where the per-sample pass reads the rows anyway) D=1 65536x183
+//              388/437; D=4 16384x60 56/59, 16384x183 120/109; D=12 4096x20
+//              21/21, 20000x10 41/39, 65536x183 610/496; D=13 4096x8 21/19; D=20
+//              4096x183 76/81, 65536x60 371/359; D=24 20000x30 109/106, 4096x183
+//              81/84; D=28 20000x30 117/110.  Up to a sample per SIMD (1024) the
+//              stores hide behind the pass's latency: D=12 1024x55 14.9/14.7,
+//              2048x55 20.8/21.4 in the kernels
 template <int MODE, int DM>
+bool use_packed(int B, int64_t n_beh, int D)
+{
+    using P = Pack<MODE, DM>;
+    if (MODE == kPoolConcat) return false;
+    auto lists = [&](int mean, int64_t n) { return n_beh >= n && n_beh >= (int64_t)mean * B; };
+    const int64_t many = 150000, half_m = 1 << 19, m = 1 << 20;
+    const int pieces = (P::two ? 2 : 1) * (D % 4 == 0 ? D / 4 : D);
+    const bool ragged = pieces >= 2 * P::lpr, wide = 8 * pieces >= 7 * P::lpr;
+    if (MODE == AMS_POOL_SUM) {
+        if (D <= 8) return lists(100, m) && B <= 16384;
+        if (ragged) return lists(20, many) || lists(10, half_m);
+        return wide ? lists(10, half_m) : lists(40, m);
+    }
+    if (MODE == AMS_POOL_MAX) return D > 8 ? lists(10, many) : D > 4 && lists(25, half_m);
+    if (D <= 4) return D > 2 && lists(100, m);
+    if (ragged) return true;
+    if (DM <= 16 || wide) return B <= 1024 || lists(10, many);
+    return lists(40, 2 * m) || (D > 20 && B >= 16384 && lists(10, many));
+}
+
+// (1) per sample: the records of its occurrences and (PACK) its packed rows;
+// attention terms c_i = g_i . u_i and da_i = sum_j ds_j e_j, ds_j = w_j (g_i .
+// e_j - c_i) (da: the query's gradient in the query mode).  An ad's upstream
+// gradient is dA_i + dA2_i where both are given.  Without packed rows `pack`
+// holds da_i, or dA_i + dA2_i, [B x D].
+template <int MODE, int DM, bool PACK>
 __global__ __launch_bounds__(kThreads) void pool_bwd_sample(int B, int D, const int32_t *__restrict__ seg_off,
                                                             int64_t n_beh, const int32_t *__restrict__ inv, int cap,
                                                             const float *__restrict__ E,
@@ -366,7 +412,9 @@ __global__ __launch_bounds__(kThreads) void pool_bwd_sample(int B, int D, const 
     const int k_ad = (int)(n_beh + i);
     // lane d holds column d of the packed rows (loaded first, used last)
     float col = 0.f, ad_col = 0.f;
-    if (MODE != kPoolConcat) {
+    if (!PACK && MODE == AMS_POOL_SUM && dA2 && lane < D)
+        pack[(size_t)i * D + lane] = (dA ? dA[(size_t)i * D + lane] : 0.f) + dA2[(size_t)i * D + lane];
+    if (PACK) {
         const int d = lane < DM ? lane : lane - DM;
         const size_t at = (size_t)i * D + d;
         if (d < D && lane < DM) {
@@ -379,7 +427,7 @@ __global__ __launch_bounds__(kThreads) void pool_bwd_sample(int B, int D, const 
         }
     }
     const int j0 = seg_off[i], j1 = seg_off[i + 1];
-    const int row_ad = MODE == kPoolConcat ? -1 - i : MODE == kPoolQuery ? -1 : (int)((unsigned)B + (unsigned)i);
+    const int row_ad = !PACK ? -1 - i : MODE == kPoolQuery ? -1 : (int)((unsigned)B + (unsigned)i);
     if (lane == 0) {
         const int one = __float_as_int(1.f);
         if (ATT) ((int4 *)rec)[k_ad] = make_int4(inv[k_ad], row_ad, one, one);
@@ -395,7 +443,7 @@ __global__ __launch_bounds__(kThreads) void pool_bwd_sample(int B, int D, const 
         }
         if (j < j1) r2[j] = make_int2(inv[j], i);
     }
-    if (MODE != kPoolConcat && lane < P::row) {
+    if (PACK && lane < P::row) {
         pack[(size_t)i * P::row + lane] = col;
         if (!ATT) pack[((size_t)B + i) * P::row + lane] = ad_col;
     }
@@ -436,8 +484,8 @@ __global__ __launch_bounds__(kThreads) void pool_bwd_sample(int B, int D, const 
         load_row_cap<DM>(E, r0, cap, D, e0);
         take(j, r0, e0);
     }
-    float mine = 0.f;                       // da's column d in lane d (query) or lane DM + d
-    constexpr int at0 = MODE == kPoolQuery ? 0 : DM;
+    float mine = 0.f;                       // da's column d in lane d, or lane DM + d (packed)
+    constexpr int at0 = MODE == kPoolQuery || !PACK ? 0 : DM;
 #pragma unroll
     for (int d = 0; d < DM; ++d) {
         const float v = ams_wave_sum(acc[d]);
@@ -445,6 +493,8 @@ __global__ __launch_bounds__(kThreads) void pool_bwd_sample(int B, int D, const 
     }
     if (MODE == kPoolQuery) {
         if (lane < D) dQ[(size_t)i * D + lane] = mine;
+    } else if (!PACK) {
+        if (lane < D) pack[(size_t)i * D + lane] = mine;
     } else if (lane < P::row) {
         pack[((size_t)B + i) * P::row + lane] = lane < DM ? ad_col : lane - DM < D ? mine : 0.f;
     }
@@ -477,70 +527,178 @@ __device__ __forceinline__ void seg_step(int u, float (&v)[DM])
 template <int DM>
 __device__ __forceinline__ void seg_scan(int u, float (&v)[DM])
 {
+    // (a scheduling barrier after each step: the moves' zeroed destinations of
+    // all six steps set up front are 6 DM registers, 129 in place of 41 at DM 16)
+    auto after = [] { __builtin_amdgcn_sched_barrier(0); };
     seg_step<0x111, 0xF, DM>(u, v);
+    after();
     seg_step<0x112, 0xF, DM>(u, v);
+    after();
     seg_step<0x114, 0xF, DM>(u, v);
+    after();
     seg_step<0x118, 0xF, DM>(u, v);
+    after();
     seg_step<0x142, 0xA, DM>(u, v);
+    after();
     seg_step<0x143, 0xC, DM>(u, v);
+    after();
 }
 
-template <int MODE, int DM>
-constexpr int seg_cpw() { return MODE == kPoolConcat ? (DM > 16 ? 2 : 4) : 1; }
+// A chunk's sums: v summed per run of equal u (lanes that are not valid hold
+// distinct u), each run's total to dE, or to the partial of its chunk where the
+// run goes on in another one.
+template <int DM>
+__device__ __forceinline__ void seg_sums(int u, bool valid, float (&v)[DM], int ch, int D,
+                                         const int32_t *__restrict__ uniq_off, float *__restrict__ dE,
+                                         float *__restrict__ head_part, float *__restrict__ tail_part,
+                                         int32_t *__restrict__ cross, int accumulate)
+{
+    const int lane = ams_lane();
+    const int c0 = ch * AMS_WAVE, c1 = c0 + AMS_WAVE;
+    seg_scan<DM>(u, v);
+    const int nu_next = __shfl_down(u, 1, AMS_WAVE);
+    const bool run_end = valid && (lane == AMS_WAVE - 1 || nu_next != u);
+    int cross_u = -1;
+    if (run_end) {
+        const int s0 = uniq_off[u], e0 = uniq_off[u + 1];
+        float *dst;
+        if (s0 < c0) {
+            dst = head_part + (size_t)ch * D;          // run began in an earlier chunk
+        } else if (e0 > c1) {
+            dst = tail_part + (size_t)ch * D;          // run starts here, continues later
+            cross_u = u;
+        } else {
+            dst = dE + (size_t)u * D;                   // whole run inside this chunk
+            if (accumulate) {
+#pragma unroll
+                for (int d = 0; d < DM; ++d)
+                    if (d < D) v[d] += dst[d];
+            }
+        }
+#pragma unroll
+        for (int d = 0; d < DM; ++d)
+            if (d < D) dst[d] = v[d];
+    }
+    // only lane 63 can end a run that continues past the chunk
+    const int cu = __shfl(cross_u, AMS_WAVE - 1, AMS_WAVE);
+    if (lane == 0) cross[ch] = cu;
+}
 
 // (2) segmented sums over chunks of 64 positions of the stable occurrence
 // order: three levels of dependent loads (the stable order; each position's
-// record; the rows), then a scan.  Bound by lines: a position's record is 16
-// bytes of a line of its own, and past the L2's 4 MB its sample's row is another
-// (12.07M positions, 65536 samples, attention: 18M lines of 128 bytes, 319 us =
-// 7.2 TB/s; with one lane per row, and rows of 48 bytes that straddle lines,
-// 443 us.  752k positions 26.9 -> 23.8 us, 2.2M 77.5 -> 54.2).  One chunk per
-// wave: two hold twice the LDS, so no more are in flight (341 us).  The
-// concatenate aggregator, whose rows are per position, reads them with one lane
-// per row, and on large grids a wave takes CPW chunks and issues each level for
-// all of them before using any.
-template <int MODE, int DM, int CPW>
+// record; the rows), then a scan.  An occurrence whose unique index is not below
+// cap is dropped: its row of dE does not exist (a capacity below the real unique
+// count, or the inverse index of a dedup that reported an internal failure,
+// where it may also be negative).  Two kernels that make the same sums of the
+// same values; use_packed says which.
+//
+// Packed rows by way of LDS.  Bound by lines: a position's record is 16 bytes of
+// a line of its own, and past the L2's 4 MB its sample's row is another (12.07M
+// positions, 65536 samples, attention: 18M lines of 128 bytes, 319 us = 7.2
+// TB/s; each row where it is 443 us.  752k positions 26.9 -> 23.8 us, 2.2M 77.5
+// -> 54.2).  One chunk per wave: two hold twice the LDS, so no more are in
+// flight (341 us).
+template <int MODE, int DM>
 __global__ __launch_bounds__(kThreads) void pool_bwd_seg(int D, int n_occ, int cap,
                                                          const int32_t *__restrict__ occ_perm,
                                                          const int32_t *__restrict__ uniq_off,
-                                                         const float *__restrict__ dU,
-                                                         const float *__restrict__ dA,
                                                          const void *__restrict__ rec,
                                                          const float *__restrict__ pack, int nch,
                                                          float *__restrict__ dE,
                                                          float *__restrict__ head_part,
                                                          float *__restrict__ tail_part,
-                                                         int32_t *__restrict__ cross, int accumulate,
-                                                         const int32_t *__restrict__ seg_off, int Lc)
+                                                         int32_t *__restrict__ cross, int accumulate)
 {
-    constexpr bool ATT = wide_rec<MODE>(), CAT = MODE == kPoolConcat;
+    constexpr bool ATT = wide_rec<MODE>();
     using P = Pack<MODE, DM>;
-    __shared__ __attribute__((aligned(16))) float stage[CAT ? 4 : kWaves * CPW * AMS_WAVE * P::row];
+    __shared__ __attribute__((aligned(16))) float stage[kWaves * AMS_WAVE * P::row];
     const int lane = ams_lane();
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / AMS_WAVE);
-    float *rows = stage + (CAT ? 0 : wave * CPW * AMS_WAVE * P::row);
-    int chv[CPW];                  // this wave's chunks (-1: none)
-    const int ch0 = (blockIdx.x * kWaves + wave) * CPW;
-    if (ch0 >= nch) return;
+    float *rows = stage + wave * AMS_WAVE * P::row;
+    const int ch = blockIdx.x * kWaves + wave;
+    if (ch >= nch) return;
+    // level 1: the stable order
+    const int p = ch * AMS_WAVE + lane;
+    const int k = p < n_occ ? occ_perm[p] : -1;
+    // level 2: the record of the position's occurrence
+    int uk = INT_MAX, si = 0;
+    float wk = 0.f, dsk = 0.f;
+    if (k >= 0) {
+        if constexpr (ATT) {
+            const int4 r = ((const int4 *)rec)[k];
+            uk = r.x;
+            si = r.y;
+            wk = __int_as_float(r.z);
+            dsk = __int_as_float(r.w);
+        } else {
+            const int2 r = ((const int2 *)rec)[k];
+            uk = r.x;
+            si = r.y;
+        }
+    }
+    // level 3: the packed row
+    const bool valid = (unsigned)uk < (unsigned)cap;
+    const bool has = valid && si != -1;       // (the query mode's ads have no gradient)
+    stage_rows<P::lpr>(pack, has ? (unsigned)si : 0u, rows, lane);
+    staged();
+    float v[DM], x[DM], y[P::two ? DM : 4];
+    staged_row<P::lpr>(rows, lane, 0, x);
+    if constexpr (P::two) staged_row<P::lpr>(rows, lane, DM / 4, y);
 #pragma unroll
-    for (int c = 0; c < CPW; ++c) chv[c] = ch0 + c < nch ? ch0 + c : -1;
+    for (int d = 0; d < DM; ++d) {
+        if (ATT) v[d] = has ? wk * x[d] + dsk * y[P::two ? d : 0] : 0.f;
+        else if (MODE == AMS_POOL_MAX) v[d] = has && __float_as_int(y[P::two ? d : 0]) == k ? x[d] : 0.f;
+        else v[d] = has ? x[d] : 0.f;
+    }
+    seg_sums<DM>(valid ? uk : -1 - lane, valid, v, ch, D, uniq_off, dE, head_part, tail_part, cross, accumulate);
+}
+
+// Each row where it is, one lane per row.  A wave takes CPW consecutive chunks
+// and issues each level of their dependent loads for all of them before using
+// any, so CPW chains of random reads are in flight per lane instead of one; each
+// chunk is then scanned and written as one.
+template <int MODE, int DM>
+constexpr int seg_cpw() { return DM > 16 || MODE == AMS_POOL_MAX ? 2 : 4; }
+
+template <int MODE, int DM, int CPW>
+__global__ __launch_bounds__(kThreads) void pool_bwd_seg_rows(int D, int n_occ, int cap,
+                                                              const int32_t *__restrict__ occ_perm,
+                                                              const int32_t *__restrict__ uniq_off,
+                                                              const float *__restrict__ A,
+                                                              const void *__restrict__ saved,
+                                                              const float *__restrict__ dU,
+                                                              const float *__restrict__ dA,
+                                                              const void *__restrict__ rec,
+                                                              const float *__restrict__ da, int nch,
+                                                              float *__restrict__ dE,
+                                                              float *__restrict__ head_part,
+                                                              float *__restrict__ tail_part,
+                                                              int32_t *__restrict__ cross, int accumulate,
+                                                              const int32_t *__restrict__ seg_off, int Lc)
+{
+    constexpr bool ATT = wide_rec<MODE>();
+    const int lane = ams_lane();
+    const int ch0 = (blockIdx.x * kWaves + threadIdx.x / AMS_WAVE) * CPW;
+    if (ch0 >= nch) return;
     // level 1: the stable order
     int k[CPW];
 #pragma unroll
     for (int c = 0; c < CPW; ++c) {
-        const int p = chv[c] * AMS_WAVE + lane;
-        k[c] = chv[c] >= 0 && p < n_occ ? occ_perm[p] : -1;
+        const int p = (ch0 + c) * AMS_WAVE + lane;
+        k[c] = p < n_occ ? occ_perm[p] : 0;
     }
-    // level 2: the record of each position's occurrence
+    // level 2: the record of each position's occurrence.  si: the sample of a
+    // behavior, -1 - i for the ad of sample i, or INT_MIN (past the end)
     int uk[CPW], si[CPW];
     float wk[CPW], dsk[CPW];
 #pragma unroll
     for (int c = 0; c < CPW; ++c) {
-        uk[c] = INT_MAX;
-        si[c] = 0;
+        const int p = (ch0 + c) * AMS_WAVE + lane;
+        uk[c] = -1;
+        si[c] = INT_MIN;
         wk[c] = 0.f;
         dsk[c] = 0.f;
-        if (k[c] >= 0) {
+        if (p < n_occ) {
             if constexpr (ATT) {
                 const int4 r = ((const int4 *)rec)[k[c]];
                 uk[c] = r.x;
@@ -554,82 +712,67 @@ __global__ __launch_bounds__(kThreads) void pool_bwd_seg(int D, int n_occ, int c
             }
         }
     }
-    // level 3: the rows each position's gradient is made of.  An occurrence
-    // whose unique index is not below cap is dropped: its row of dE does not
-    // exist (a capacity below the real unique count, or the inverse index of a
-    // dedup that reported an internal failure, where it may also be negative).
-    float r[CAT ? CPW : 1][DM];  // concat: the behavior's slice of dU, or the ad's dA
-    if constexpr (CAT) {
+    // level 3: the rows each position's gradient is made of
+    float r[CPW][DM];            // dU of the behavior's sample (concat: its slice), or the ad's dA
+    float a[ATT ? CPW : 1][DM];  // attentive: the sample's query row, or the ad's attention term da
+    int am[MODE == AMS_POOL_MAX ? CPW : 1][DM];
 #pragma unroll
-        for (int c = 0; c < CPW; ++c) {
-            const bool valid = (unsigned)uk[c] < (unsigned)cap;
-            const int i = si[c] >= 0 ? si[c] : -1 - si[c];
+    for (int c = 0; c < CPW; ++c) {
+        const bool valid = si[c] != INT_MIN && (unsigned)uk[c] < (unsigned)cap;
+        const bool beh = valid && si[c] >= 0;
+        const bool ad = valid && si[c] < 0 && MODE != kPoolQuery;
+        const int i = beh ? si[c] : (ad ? -1 - si[c] : 0);
 #pragma unroll
-            for (int d = 0; d < DM; ++d) r[c][d] = 0.f;
-            if (valid && si[c] >= 0) {
-                const int pos = k[c] - seg_off[i];
-                if (pos < Lc) load_row<DM>(dU + (size_t)i * Lc * D, pos, D, r[c]);
-            }
-            if (valid && si[c] < 0 && dA) load_row<DM>(dA, i, D, r[c]);
+        for (int d = 0; d < DM; ++d) r[c][d] = 0.f;
+        if (beh && MODE != kPoolConcat) load_row<DM>(dU, i, D, r[c]);
+        if (beh && MODE == kPoolConcat) {
+            const int pos = k[c] - seg_off[i];
+            if (pos < Lc) load_row<DM>(dU + (size_t)i * Lc * D, pos, D, r[c]);
         }
-    } else {
+        if (ad && dA) load_row<DM>(dA, i, D, r[c]);
+        if constexpr (MODE == AMS_POOL_MAX) {
+            const int32_t *amr = (const int32_t *)saved + (size_t)i * D;
 #pragma unroll
-        for (int c = 0; c < CPW; ++c)
-            stage_rows<P::lpr>(pack, (unsigned)uk[c] < (unsigned)cap && si[c] != -1 ? (unsigned)si[c] : 0u,
-                               rows + c * AMS_WAVE * P::row, lane);
-        staged();
+            for (int d = 0; d < DM; ++d) am[c][d] = (beh && d < D) ? amr[d] : -1;
+        }
+        if constexpr (ATT) {
+#pragma unroll
+            for (int d = 0; d < DM; ++d) a[c][d] = 0.f;
+            if (beh) load_row<DM>(A, i, D, a[c]);
+            if (ad && MODE == AMS_POOL_ATT) load_row<DM>(da, i, D, a[c]);
+        }
     }
     // each chunk: its positions' gradients, summed per run of one image
 #pragma unroll
     for (int c = 0; c < CPW; ++c) {
-        const int ch = chv[c];
-        if (ch < 0) break;
-        const int c0 = ch * AMS_WAVE, c1 = c0 + AMS_WAVE;
-        const bool valid = (unsigned)uk[c] < (unsigned)cap;
-        int u = valid ? uk[c] : -1 - lane;       // distinct per invalid lane: never joins a run
+        const int ch = ch0 + c;
+        if (ch >= nch) break;
+        const bool valid = si[c] != INT_MIN && (unsigned)uk[c] < (unsigned)cap;
+        const bool beh = valid && si[c] >= 0;
+        const int u = valid ? uk[c] : -1 - lane;  // distinct per invalid lane: never joins a run
         float v[DM];
-        if constexpr (CAT) {
+#pragma unroll
+        for (int d = 0; d < DM; ++d) v[d] = 0.f;
+        if (beh) {
+            if (MODE == AMS_POOL_SUM || MODE == kPoolConcat) {
+#pragma unroll
+                for (int d = 0; d < DM; ++d) v[d] = r[c][d];
+            } else if (MODE == AMS_POOL_MAX) {
+#pragma unroll
+                for (int d = 0; d < DM; ++d) v[d] = am[MODE == AMS_POOL_MAX ? c : 0][d] == k[c] ? r[c][d] : 0.f;
+            } else {   // attentive: w_j g_i + ds_j a_i; A holds the query rows in the query mode
+#pragma unroll
+                for (int d = 0; d < DM; ++d) v[d] = wk[c] * r[c][d] + dsk[c] * a[ATT ? c : 0][d];
+            }
+        } else if (valid && MODE != kPoolQuery) {   // an ad: dA (+ the attention term)
 #pragma unroll
             for (int d = 0; d < DM; ++d) v[d] = r[c][d];
-        } else {
-            float x[DM], y[P::two ? DM : 4];
-            staged_row<P::lpr>(rows + c * AMS_WAVE * P::row, lane, 0, x);
-            if constexpr (P::two) staged_row<P::lpr>(rows + c * AMS_WAVE * P::row, lane, DM / 4, y);
-            const bool has = valid && si[c] != -1;   // (the query mode's ads have no gradient)
+            if (MODE == AMS_POOL_ATT) {
 #pragma unroll
-            for (int d = 0; d < DM; ++d) {
-                if (ATT) v[d] = has ? wk[c] * x[d] + dsk[c] * y[P::two ? d : 0] : 0.f;
-                else if (MODE == AMS_POOL_MAX) v[d] = has && __float_as_int(y[P::two ? d : 0]) == k[c] ? x[d] : 0.f;
-                else v[d] = has ? x[d] : 0.f;
+                for (int d = 0; d < DM; ++d) v[d] += a[ATT ? c : 0][d];
             }
         }
-        seg_scan<DM>(u, v);
-        const int nu_next = __shfl_down(u, 1, AMS_WAVE);
-        const bool run_end = valid && (lane == AMS_WAVE - 1 || nu_next != u);
-        int cross_u = -1;
-        if (run_end) {
-            const int s0 = uniq_off[u], e0 = uniq_off[u + 1];
-            float *dst;
-            if (s0 < c0) {
-                dst = head_part + (size_t)ch * D;          // run began in an earlier chunk
-            } else if (e0 > c1) {
-                dst = tail_part + (size_t)ch * D;          // run starts here, continues later
-                cross_u = u;
-            } else {
-                dst = dE + (size_t)u * D;                   // whole run inside this chunk
-                if (accumulate) {
-#pragma unroll
-                    for (int d = 0; d < DM; ++d)
-                        if (d < D) v[d] += dst[d];
-                }
-            }
-#pragma unroll
-            for (int d = 0; d < DM; ++d)
-                if (d < D) dst[d] = v[d];
-        }
-        // only lane 63 can end a run that continues past the chunk
-        const int cu = __shfl(cross_u, AMS_WAVE - 1, AMS_WAVE);
-        if (lane == 0) cross[ch] = cu;
+        seg_sums<DM>(u, valid, v, ch, D, uniq_off, dE, head_part, tail_part, cross, accumulate);
     }
 }
 
@@ -702,8 +845,8 @@ template <int DM>
 constexpr int fix_short() { return DM > 16 ? 2 : 4; }
 
 // Below this many 64-position chunks the backward runs one chunk per wave
-// (the concatenate aggregator's stable-order pass and the fix-up): the grid is
-// then small enough that more waves, not longer ones, keep the part busy.
+// (the stable-order pass without packed rows, and the fix-up): the grid is then
+// small enough that more waves, not longer ones, keep the part busy.
 constexpr int kSmallChunks = 16384;
 
 // (3b) the fix-up of a run that starts in chunk ch and crosses chunk edges:
@@ -853,7 +996,7 @@ struct PoolPlan {
 
 // Workspace of the backward; the records are 16 bytes with attention
 // (ams_pool_workspace's AMS_POOL_ATT also covers the query mode), 8 without;
-// two packed rows per sample, of 64 or 128 bytes per half.
+// two packed rows per sample, of 64 or 128 bytes per half (also room for [B x D]).
 PoolPlan plan_pool(int32_t mode, int32_t B, int64_t n_beh, int32_t D)
 {
     PoolPlan p{};
@@ -895,17 +1038,32 @@ void launch_bwd(int B, int D, const int32_t *seg_off, int64_t n_beh, const int32
     // head and tail rows start at 256-byte boundaries, so rows of D == DM
     // floats (D a multiple of 4) are 16-byte aligned
     const bool full = D == DM;
-    if (B > 0)
-        AMS_LAUNCH("pool_bwd_sample", st, pool_bwd_sample<MODE, DM><<<(B + kWaves - 1) / kWaves, kThreads, 0, st>>>(
-            B, D, seg_off, n_beh, inv, cap, E, U, A, saved, dU, dA, dA2, rec, pack, dQ));
     const bool small = p.nch < kSmallChunks;
+    const int cap_seg = cap < n_occ ? cap : n_occ;
+    const bool packed = use_packed<MODE, DM>(B, n_beh, D);
+#define SAMPLE_LAUNCH(PACKV)                                                                                 \
+    AMS_LAUNCH("pool_bwd_sample", st, (pool_bwd_sample<MODE, DM, PACKV><<<(B + kWaves - 1) / kWaves, kThreads, 0, st>>>( \
+                                          B, D, seg_off, n_beh, inv, cap, E, U, A, saved, dU, dA, dA2, rec, pack, dQ)))
 #define SEG_LAUNCH(CPWV)                                                                                     \
-    AMS_LAUNCH("pool_bwd_seg", st, (pool_bwd_seg<MODE, DM, CPWV><<<(p.nch + kWaves * CPWV - 1) / (kWaves * CPWV), \
-                                                                  kThreads, 0, st>>>(                        \
-                                       D, n_occ, min(cap, n_occ), occ_perm, uniq_off, dU, dA, rec, pack, p.nch, dE, head, tail, \
-                                       cross, accumulate, seg_off, Lc)))
-    if (small) SEG_LAUNCH(1);
-    else SEG_LAUNCH((seg_cpw<MODE, DM>()));
+    AMS_LAUNCH("pool_bwd_seg_rows", st, (pool_bwd_seg_rows<MODE, DM, CPWV>                             \
+                                                <<<(p.nch + kWaves * CPWV - 1) / (kWaves * CPWV), kThreads, 0, st>>>( \
+                                       D, n_occ, cap_seg, occ_perm, uniq_off, A, saved, dU, dA, rec, pack, p.nch, dE, \
+                                       head, tail, cross, accumulate, seg_off, Lc)))
+    if constexpr (MODE != kPoolConcat) {
+        if (packed) {
+            if (B > 0) SAMPLE_LAUNCH(true);
+            AMS_LAUNCH("pool_bwd_seg", st, (pool_bwd_seg<MODE, DM><<<(p.nch + kWaves - 1) / kWaves, kThreads, 0, st>>>(
+                                               D, n_occ, cap_seg, occ_perm, uniq_off, rec, pack, p.nch, dE, head, tail,
+                                               cross, accumulate)));
+        }
+    }
+    if (!packed) {
+        if (B > 0) SAMPLE_LAUNCH(false);
+        if (MODE == AMS_POOL_SUM && dA2) dA = pack;
+        if (small) SEG_LAUNCH(1);
+        else SEG_LAUNCH((seg_cpw<MODE, DM>()));
+    }
+#undef SAMPLE_LAUNCH
 #undef SEG_LAUNCH
     // a whole block of chunks inside one run's head chunks starts at block 1
     // or later (the run starts in an earlier chunk), so it needs 2 blocks

@@ -1,4 +1,5 @@
-"""The pooling backward's packed rows against plain float64: every row width
+"""The pooling backward against plain float64, with its rows packed and read where
+they are (the rule between the two is checked on both sides): every row width
 (columns short of, at and past the 12, 16 and 32 that a packed half holds),
 chunks of the stable order that are full, short by one and over by one, samples
 without behaviors, ads without an upstream gradient, a capacity below the unique
@@ -33,6 +34,34 @@ def batch(B, n_occ, n_ids, g):
     (50, 2047, 17), (21, 1025, 31), (70, 5000, 32), (300, 70_000, 12),
 ])
 def test_pool_backward_rows(mode, B, n_occ, D):
+    check(mode, B, n_occ, D)
+
+
+# Where the rule between packed rows and rows read where they are changes its
+# answer: mode, D, samples, and the fewest behaviors that are packed (with one
+# behavior less they are not).  Mean lists of 10, 20, 25, 40 and 100, batches of
+# 150,000 to 2^21, rows in whole 16-byte pieces and not.
+@pytest.mark.parametrize("mode,D,B,n_beh", [
+    ("sum", 8, 9000, 2**20), ("sum", 3, 10_487, 1_048_700), ("sum", 10, 7001, 150_000), ("sum", 13, 52_431, 524_310),
+    ("sum", 12, 20_001, 2**20), ("sum", 16, 9999, 2**19), ("sum", 20, 2**10, 2**20), ("sum", 32, 52_429, 524_290),
+    ("max", 5, 20_973, 524_325), ("max", 8, 1000, 2**19), ("max", 12, 4001, 150_000), ("max", 17, 15_007, 150_070),
+    ("max", 32, 2000, 150_000), ("att", 4, 8001, 2**20), ("att", 6, 3333, 150_000), ("att", 12, 15_003, 150_030),
+    ("att", 16, 2049, 150_000), ("att", 24, 16_384, 163_840), ("att", 28, 5001, 150_000), ("att", 20, 4097, 2**21),
+    ("query", 12, 9001, 150_000), ("query", 20, 52_429, 2_097_160), ("query", 32, 1025, 150_000),
+])
+def test_pool_backward_routes(mode, D, B, n_beh):
+    for n, kernel in ((n_beh, "pool_bwd_seg"), (n_beh - 1, "pool_bwd_seg_rows")):
+        ams.ams_timing_read()
+        ams.ams_timing_enable(True)
+        try:
+            check(mode, B, n + B, D, full_only=True)
+            ran = ams.ams_timing_read()
+        finally:
+            ams.ams_timing_enable(False)
+        assert kernel in ran and len({"pool_bwd_seg", "pool_bwd_seg_rows"} & set(ran)) == 1
+
+
+def check(mode, B, n_occ, D, full_only=False):
     print(f"pool rows {mode} B={B} n_occ={n_occ} D={D}", flush=True)
     g = torch.Generator(device="cuda").manual_seed(n_occ + D)
     n_beh, seg, inv, perm, off, sample, n_u = batch(B, n_occ, max(2, n_occ // 3), g)
@@ -61,7 +90,7 @@ def test_pool_backward_rows(mode, B, n_occ, D):
 
     i32 = lambda t: t.int().contiguous()  # noqa: E731
     nu = torch.tensor([n_u], dtype=torch.int32, device="cuda")
-    for cap in {n_u, max(1, n_u // 2), n_u + 9}:
+    for cap in {n_u} if full_only else {n_u, max(1, n_u // 2), n_u + 9}:
         rows = min(cap, n_u)
         Ec = torch.zeros((cap, D), device="cuda")
         Ec[:rows] = E[:rows]
