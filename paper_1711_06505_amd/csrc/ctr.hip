@@ -674,8 +674,11 @@ inline size_t ctr_lds_bytes(const CtrArgs &a)
 }
 
 // Which widths the calls take: the sum of the nets' activations, twice, and of
-// the parts of a 512-thread block's widest layer has to fit the LDS (a bound
-// the kernels' own need never passes).
+// the parts of a 512-thread block's widest layer has to fit the LDS.  What the
+// kernels themselves need, with rows padded to whole quads and parts of whole
+// 64-column blocks, is a little more (72-200-80-2: 79,936 bytes where this says
+// 77,632) and is checked beside it; the widest CTR net takes 117,824 bytes, so on
+// a device with 160 KB for a block only this rule refuses one.
 inline size_t net_width_bytes(const CtrArgs *const *nets, int count)
 {
     int act = 0, parts = 0;
@@ -1191,6 +1194,7 @@ extern "C" ams_status ams_ctr_fwd_bwd(const ams_ctr *net, int32_t B, int32_t n_f
     const CtrArgs *nets[] = {&a};
     if (net_width_bytes(nets, 1) > lds_limit()) return AMS_ERR_DIMS;
     const size_t lds = ctr_lds_bytes(a);
+    if (lds > lds_limit()) return AMS_ERR_DIMS;
     const int G = (B + kCtrBS - 1) / kCtrBS;
     const int PS = net_part_size(a) + 4;
     if (!ws || ws_bytes < (size_t)G * PS * 4) return AMS_ERR_WORKSPACE;
