@@ -45,17 +45,19 @@
  *             floats.  IDs are int32.
  * Precision:  AMS_F32: T and W float32, float32 MFMA with float32 accumulation.
  *             AMS_F32_X3: T and W float32 as AMS_F32.  The 4096-wide layer's
- *             forward product (dims[1] a multiple of 256) and, when dims[0] is
- *             a multiple of 128, its weight gradient run on bf16 MFMA: every
- *             float32 operand (T, W1, the activation gradient) is split
- *             exactly into three bf16 parts h + m + l (round to nearest at
- *             each step; exact for |x| >= 2^-100, where all parts are normal)
- *             and six of the nine part products (hh, hm, mh, hl, lh, mm) are
- *             accumulated in float32, hh in an accumulator of its own; the
- *             three left out stay below 2^-22 |x y| per product, about one
- *             float32 rounding.  A product with a non-finite operand may be
- *             NaN where float32 gives an infinity.  Everything else as
- *             AMS_F32.
+ *             forward product (dims[1] a multiple of 256) and, when dims[1] is
+ *             256 and dims[0] a multiple of 128, its weight gradient run on
+ *             bf16 MFMA: every float32 operand (T, W1, the activation
+ *             gradient) is split exactly into three bf16 parts h + m + l
+ *             (round to nearest at each step) and six of the nine part
+ *             products (hh, hm, mh, hl, lh, mm) are accumulated in float32,
+ *             hh in an accumulator of its own; the three left out stay below
+ *             2^-22 |x y| per product, about one float32 rounding.  The weight
+ *             gradient does so over all of float32's range, and gives the
+ *             infinities and NaN that float32 gives.  In the forward product
+ *             the split is exact for |x| >= 2^-110, and one with an operand
+ *             that is not finite, or rounds to infinity in bf16, may be NaN
+ *             where float32 gives an infinity.  Everything else as AMS_F32.
  *             AMS_BF16: T and W bfloat16; bf16 MFMA with float32 accumulation
  *             for the 4096-wide layer and its weight gradient (whose
  *             activation-gradient operand is rounded to bf16).  The smaller

@@ -2159,7 +2159,85 @@ __device__ __forceinline__ float tb_dzl(brsrc_t rdE, brsrc_t rE, int final_relu,
     return (d < D && (!final_relu || e > 0.f)) ? g : 0.f;
 }
 
-// X3: dZ1 leaves as the three bf16 parts of AMS_F32_X3, planes [cap x H].
+// The parts of AMS_F32_X3's first weight gradient are those of 2^16 x: the last
+// bits of every float32, subnormals included, are then bf16 numbers (the least
+// is 2^-133).  A gradient that is too large for that (kDwxMax, infinities, NaN) is
+// stored as a NaN and its own 32 bits.
+constexpr float kDwxScale = 0x1p16f, kDwxMax = 0x1p111f;
+constexpr uint16_t kDwxRaw = 0x7fff;
+
+__device__ __forceinline__ float dwx_value(uint16_t h, uint16_t m, uint16_t l)
+{
+    if (h == kDwxRaw) return __uint_as_float(((uint32_t)m << 16) | l);
+    return ((ams_bf16_to_f32(h) + ams_bf16_to_f32(m)) + ams_bf16_to_f32(l)) * (1.f / kDwxScale);
+}
+
+// x0 and x1 without their bf16 parts h (x0's in the low half): one instruction
+// each, exact over the whole range, subnormals too (the products by one and zero
+// and the sum have no rounding; compared bit by bit with the subtractions).  The
+// unit vectors stay in registers: as constants the compiler makes them inline
+// operands, which this instruction reads as another pair.
+struct DwxUnits {
+    uint32_t lo, hi;
+};
+
+__device__ __forceinline__ DwxUnits dwx_units()
+{
+    DwxUnits u = {0x0000bf80u, 0xbf800000u};              // (-1, 0), (0, -1)
+    asm("" : "+s"(u.lo), "+s"(u.hi));
+    return u;
+}
+
+__device__ __forceinline__ void dwx_rest(uint32_t h, const DwxUnits &u, float &x0, float &x1)
+{
+    const bf16x2 v = __builtin_bit_cast(bf16x2, h);
+    x0 = __builtin_amdgcn_fdot2_f32_bf16(v, __builtin_bit_cast(bf16x2, u.lo), x0, false);
+    x1 = __builtin_amdgcn_fdot2_f32_bf16(v, __builtin_bit_cast(bf16x2, u.hi), x1, false);
+}
+
+// The parts of 2^16 z for N values, two per word.  Where a high part is not
+// finite, the residuals of its pair are not either: one sum says whether the wave
+// has any such value.
+template <int N>
+__device__ __forceinline__ void dwx_split(const float *z, const DwxUnits &un, uint32_t (&p)[3][N / 2])
+{
+    float odd = 0.f;
+#pragma unroll
+    for (int e = 0; e < N / 2; ++e) {
+        float x0 = kDwxScale * z[2 * e], x1 = kDwxScale * z[2 * e + 1];
+        p[0][e] = cvt_pk_bf16(x0, x1);
+        dwx_rest(p[0][e], un, x0, x1);
+        odd = fmaf(x0, 0.f, fmaf(x1, 0.f, odd));
+        p[1][e] = cvt_pk_bf16(x0, x1);
+        dwx_rest(p[1][e], un, x0, x1);
+        p[2][e] = cvt_pk_bf16(x0, x1);
+    }
+    if (ams_ballot(!(odd == 0.f)) == 0) return;
+#pragma unroll
+    for (int e = 0; e < N / 2; ++e) {
+        const bool in0 = fabsf(z[2 * e]) < kDwxMax, in1 = fabsf(z[2 * e + 1]) < kDwxMax;
+        if (in0 && in1) continue;
+        // the pair's parts one by one
+        uint16_t q[3][2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const float v = z[2 * e + i], x = kDwxScale * v;
+            const uint32_t bits = __float_as_uint(v);
+            const uint16_t h = ams_f32_to_bf16(x);
+            const float r1 = x - ams_bf16_to_f32(h);
+            const uint16_t m = ams_f32_to_bf16(r1);
+            const bool in = i ? in1 : in0;
+            q[0][i] = in ? h : kDwxRaw;
+            q[1][i] = in ? m : (uint16_t)(bits >> 16);
+            q[2][i] = in ? ams_f32_to_bf16(r1 - ams_bf16_to_f32(m)) : (uint16_t)bits;
+        }
+#pragma unroll
+        for (int k = 0; k < 3; ++k) p[k][e] = q[k][0] | ((uint32_t)q[k][1] << 16);
+    }
+}
+
+// X3: dZ1 leaves as the three bf16 parts of AMS_F32_X3, planes [cap x H] (H is
+// 256, every column exists).
 template <int L, int SD, typename TW, typename TH, bool PR, bool X3 = false>
 __global__ __launch_bounds__(kTbThreads) void tail_bwd(const TH *__restrict__ H1s,
                                                         const float *__restrict__ H2s,
@@ -2240,6 +2318,7 @@ __global__ __launch_bounds__(kTbThreads) void tail_bwd(const TH *__restrict__ H1
         const brsrc_t rH2 = make_buf(L == 3 ? H2s + (size_t)c0 * M : dE, L == 3 ? nr * M * 4 : 0);
         const brsrc_t rH1 = make_buf(H1s + (size_t)c0 * H, nr * H * (uint32_t)sizeof(TH));
         const brsrc_t rZ1 = make_buf(dZ1 + (size_t)c0 * H, X3 ? 0 : nr * H * (uint32_t)sizeof(TH));
+        const DwxUnits units = dwx_units();
         brsrc_t rPl[3];
         if (X3)
 #pragma unroll
@@ -2314,26 +2393,28 @@ __global__ __launch_bounds__(kTbThreads) void tail_bwd(const TH *__restrict__ H1
             // dZ1 = dH1 * [H1 > 0], written out (stores past the chunk are
             // dropped by the descriptor; columns past H are not stored); db1
             const int icol = i0 + 32 * ib + r32;
-            float cs = 0.f, css = 0.f;
+            float cs = 0.f, css = 0.f, dzv[X3 ? 16 : 1];
 #pragma unroll
             for (int jj = 0; jj < 16; ++jj) {
                 const bool pos = h1v[ib][jj] > 0.f;
                 const float dz = pos ? a1[ib][jj] : (PR ? sl1[ib] * a1[ib][jj] : 0.f);
                 cs += dz;
                 if (PR) css += pos ? 0.f : a1[ib][jj] * h1v[ib][jj];
-                if constexpr (X3) {
-                    if (icol < H) {
-                        const uint32_t e = 2u * (uint32_t)(acc_row(jj, lane) * H + icol);
-                        const uint16_t ph = ams_f32_to_bf16(dz);
-                        const float r1 = dz - ams_bf16_to_f32(ph);
-                        const uint16_t pm = ams_f32_to_bf16(r1);
-                        const float r2 = r1 - ams_bf16_to_f32(pm);
-                        __builtin_amdgcn_raw_buffer_store_b16(ph, rPl[0], e, 0, 0);
-                        __builtin_amdgcn_raw_buffer_store_b16(pm, rPl[1], e, 0, 0);
-                        __builtin_amdgcn_raw_buffer_store_b16(ams_f32_to_bf16(r2), rPl[2], e, 0, 0);
-                    }
-                } else if (icol < H) {
-                    buf_st<TH>(rZ1, (uint32_t)(acc_row(jj, lane) * H + icol), dz);
+                if constexpr (X3) dzv[jj] = dz;
+                else if (icol < H) buf_st<TH>(rZ1, (uint32_t)(acc_row(jj, lane) * H + icol), dz);
+            }
+            if constexpr (X3) {
+#pragma unroll
+                for (int j0 = 0; j0 < 16; j0 += 4) {
+                    uint32_t pl[3][2];
+                    dwx_split<4>(dzv + j0, units, pl);
+#pragma unroll
+                    for (int q = 0; q < 3; ++q)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+                            __builtin_amdgcn_raw_buffer_store_b16((uint16_t)(pl[q][e / 2] >> (16 * (e & 1))), rPl[q],
+                                                                  2u * (uint32_t)(acc_row(j0 + e, lane) * H + icol), 0,
+                                                                  0);
                 }
             }
             db1a[ib] += cs + __shfl_xor(cs, 32, AMS_WAVE);
@@ -2977,11 +3058,15 @@ __device__ __forceinline__ void dwtr_compute(const float *slot, v16f *acc, int l
 // read.  The products of the two high parts have an accumulator of their own:
 // the sums that carry the result's rounding are then 1/6 as many as with one
 // accumulator, and the error against float64 is half the float32 MFMA's.
-// 20011 rows: 346 us in float32 MFMA, 250-257 us so (1.0 PFLOP/s of part
-// products, what a large bf16 matrix product reaches on this card; 12900 rows:
-// 224 and 160-183).  Ordering the LDS reads, the splits and the MFMAs by
-// scheduling groups (263 us) or raising the waves' priority over the products
-// (no change) did not help.
+// Both operands are scaled by 2^16 before they are split (and the sums by 2^-32
+// at the end), so that the parts of the smallest float32 values are bf16 numbers
+// too; a tile with a result that is not finite is made again by dwx_plain.
+// 20011 rows: 346 us in float32 MFMA, 263 us so (0.96 PFLOP/s of part products;
+// 12900 rows: 226 and 170), of which the features' scaling takes 7 and the check
+// of the results 1.  Ordering the LDS reads, the splits and the MFMAs by
+// scheduling groups, raising the waves' priority over the products and
+// dwx_rest's instruction in place of the split's subtractions (264 us, the tail's
+// 56 us become 54) did not help.
 //
 // A stage is 32 images: the feature rows' 128 columns in float32 (16 KB, 16-byte
 // chunks of rows 8-15 and 24-31 at chunk ^ 8: a wave's 4-byte reads take rows
@@ -3037,7 +3122,7 @@ __device__ __forceinline__ void dwx_compute(const float *slot, v16f (&acc)[4], v
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
                 const int row = 16 * kk + 8 * h + j, col = wn * 64 + nb * 32 + r32;
-                x[nb][j] = slot[row * R::BN + (col ^ (dwx_swz(row) << 2))];
+                x[nb][j] = kDwxScale * slot[row * R::BN + (col ^ (dwx_swz(row) << 2))];
             }
         uint4 a[3][2];
 #pragma unroll
@@ -3065,6 +3150,44 @@ __device__ __forceinline__ void dwx_compute(const float *slot, v16f (&acc)[4], v
                 acc[mb * 2 + nb] = mfma_bf16(a[0][mb], bh, acc[mb * 2 + nb]);
             }
         }
+    }
+}
+
+// The tile in float32 MFMA, for the calls where a value or a sum leaves the range
+// of the parts (a result is then not finite): the same infinities and NaN as in
+// the float32 mode.  Plain loops, a stage of 32 images at a time in the slots.
+__device__ __forceinline__ void dwx_plain(const float *__restrict__ T, int64_t n_rows, int F,
+                                          const int32_t *__restrict__ uniq, const uint16_t *__restrict__ planes,
+                                          size_t plane, int n0, int u0, int u1, float *za, float *tb, v16f (&acc)[4])
+{
+    using R = DwX3;
+    const int t = threadIdx.x, lane = ams_lane(), wave = t / AMS_WAVE;
+    const int h = lane >> 5, r32 = lane & 31, wm = wave >> 1, wn = wave & 1;
+#pragma unroll
+    for (int x = 0; x < 4; ++x) acc[x] = (v16f){};
+#pragma unroll 1
+    for (int ub = u0; ub < u1; ub += R::BK) {
+        __syncthreads();
+#pragma unroll 1
+        for (int i = t; i < R::BK * R::BM; i += kDwThreads) {
+            const int u = ub + i / R::BM;
+            const size_t e = (size_t)u * R::BM + i % R::BM;
+            za[i] = u < u1 ? dwx_value(planes[e], planes[plane + e], planes[2 * plane + e]) : 0.f;
+        }
+#pragma unroll 1
+        for (int i = t; i < R::BK * R::BN; i += kDwThreads) {
+            const int u = ub + i / R::BN, id = u < u1 ? uniq[u] : -1;
+            tb[i] = id >= 0 && (int64_t)id < n_rows ? T[(size_t)id * F + n0 + i % R::BN] : 0.f;
+        }
+        __syncthreads();
+#pragma unroll 1
+        for (int k = h; k < R::BK; k += 2)
+#pragma unroll
+            for (int mb = 0; mb < 2; ++mb)
+#pragma unroll
+                for (int nb = 0; nb < 2; ++nb)
+                    acc[mb * 2 + nb] = mfma_f32(za[k * R::BM + wm * 64 + mb * 32 + r32],
+                                                tb[k * R::BN + wn * 64 + nb * 32 + r32], acc[mb * 2 + nb]);
     }
 }
 
@@ -3123,6 +3246,16 @@ __global__ __launch_bounds__(kDwThreads) void dw1_part_x3(const float *__restric
 #undef DWX_STAGE
         AMS_WAIT_VM(0);
     }
+    bool odd = false;
+#pragma unroll
+    for (int x = 0; x < 4; ++x)
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {
+            const float v = acc[x][j] + low[x][j];
+            odd |= !(fabsf(v) < INFINITY);
+            acc[x][j] = v * (1.f / (kDwxScale * kDwxScale));
+        }
+    if (__syncthreads_or(odd)) dwx_plain(T, n_rows, F, uniq, planes, plane, n0, u0, u1, ring0, ring1, acc);
 
     float *out = part + (size_t)c * R::BM * F;
 #pragma unroll
@@ -3133,7 +3266,7 @@ __global__ __launch_bounds__(kDwThreads) void dw1_part_x3(const float *__restric
 #pragma unroll
             for (int j = 0; j < 16; ++j) {
                 const int row = (wave >> 1) * 64 + mb * 32 + acc_row(j, lane);
-                out[(size_t)row * F + col] = acc[mb * 2 + nb][j] + low[mb * 2 + nb][j];
+                out[(size_t)row * F + col] = acc[mb * 2 + nb][j];
             }
         }
 }
