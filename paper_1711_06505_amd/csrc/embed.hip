@@ -75,6 +75,12 @@ __device__ __forceinline__ v16f mfma_bf16(uint4 a, uint4 b, v16f c)
                                                    __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
 }
 
+__device__ __forceinline__ uint32_t cvt_pk_bf16(float a, float b)
+{
+    const bf16x2 v = {(__bf16)a, (__bf16)b};      // round to nearest even
+    return __builtin_bit_cast(uint32_t, v);
+}
+
 // Row index of element j of a 32x32 MFMA accumulator held by `lane`
 // (column = lane % 32).
 __device__ __forceinline__ int acc_row(int j, int lane) { return 8 * (j >> 2) + 4 * (lane >> 5) + (j & 3); }
@@ -474,10 +480,13 @@ __device__ __forceinline__ void sk_compute(const float *slot, v16f (*acc)[kSkNB]
 // units.  whole: the segment covered the tile's full K, so H1 = act(acc + b1)
 // is written (b1 alone for a row whose ID is out of range; keep_z keeps the
 // pre-activation); otherwise acc goes to this worker's partial tile `piece`
-// (sk_piece_off: 512 contiguous bytes per store of 32 lanes).
+// (sk_piece_off: 512 contiguous bytes per store of 32 lanes).  b1s: the tile's
+// 256 biases in LDS, staged with the row IDs.  (Three rows of a 320-256-16 net
+// in bf16, the layer: 18.2 us with the biases read from memory here, four round
+// trips, and bf16 rounding in integer instructions, 12.3 us so.)
 template <int MB>
 __device__ __forceinline__ void sk_store(const v16f (&acc)[MB][kSkNB], bool whole, const int *rid, int m0, int n0,
-                                         int n_u, int H, const float *__restrict__ b1, int keep_z,
+                                         int n_u, int H, const float *b1s, int keep_z,
                                          float *__restrict__ H1, uint16_t *__restrict__ H1b,
                                          uint16_t *__restrict__ H1lo, float *__restrict__ piece, int lane, int wave)
 {
@@ -490,10 +499,7 @@ __device__ __forceinline__ void sk_store(const v16f (&acc)[MB][kSkNB], bool whol
         for (int nb = 0; nb < kSkNB; ++nb) {
             float4 bias[4];
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const float *bp = b1 + n0 + c0 + nb * 32 + 8 * q;        // (b1 may start anywhere)
-                bias[q] = make_float4(bp[0], bp[1], bp[2], bp[3]);
-            }
+            for (int q = 0; q < 4; ++q) bias[q] = *(const float4 *)&b1s[c0 + nb * 32 + 8 * q];
 #pragma unroll
             for (int mb = 0; mb < MB; ++mb) {
                 const int r = rl0 + mb * 32;
@@ -511,17 +517,12 @@ __device__ __forceinline__ void sk_store(const v16f (&acc)[MB][kSkNB], bool whol
                     const size_t o = (size_t)(m0 + r) * H + n0 + c0 + nb * 32 + 8 * q;
                     if (H1) *(float4 *)(H1 + o) = make_float4(z[0], z[1], z[2], z[3]);
                     if (H1b) {
-                        uint16_t hi[4], lo[4];
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) {
-                            hi[e] = ams_f32_to_bf16(z[e]);
-                            lo[e] = ams_f32_to_bf16(z[e] - ams_bf16_to_f32(hi[e]));
-                        }
-                        *(uint2 *)(H1b + o) =
-                            make_uint2(hi[0] | ((uint32_t)hi[1] << 16), hi[2] | ((uint32_t)hi[3] << 16));
+                        const uint2 hi = make_uint2(cvt_pk_bf16(z[0], z[1]), cvt_pk_bf16(z[2], z[3]));
+                        *(uint2 *)(H1b + o) = hi;
                         if (H1lo)
-                            *(uint2 *)(H1lo + o) =
-                                make_uint2(lo[0] | ((uint32_t)lo[1] << 16), lo[2] | ((uint32_t)lo[3] << 16));
+                            *(uint2 *)(H1lo + o) = make_uint2(
+                                cvt_pk_bf16(z[0] - __uint_as_float(hi.x << 16), z[1] - __uint_as_float(hi.x & 0xffff0000u)),
+                                cvt_pk_bf16(z[2] - __uint_as_float(hi.y << 16), z[3] - __uint_as_float(hi.y & 0xffff0000u)));
                     }
                 }
             }
@@ -558,6 +559,7 @@ __global__ __launch_bounds__(kSkThreads) void l1sk(const TT *__restrict__ T, int
     __shared__ __attribute__((aligned(16))) float ring1[K::SLOT];
     __shared__ __attribute__((aligned(16))) float ring2[K::SLOT];
     __shared__ int rid[K::BM];
+    __shared__ __attribute__((aligned(16))) float b1s[kSkBN];
 
     const int n_u = min(*n_uniq_p, cap);
     if (n_u <= 0) return;
@@ -583,6 +585,7 @@ __global__ __launch_bounds__(kSkThreads) void l1sk(const TT *__restrict__ T, int
             }
             rid[t] = id;
         }
+        if (t >= kSkThreads - kSkBN && ks == 0 && ke == S) b1s[t - (kSkThreads - kSkBN)] = b1[n0 + t - (kSkThreads - kSkBN)];
         __syncthreads();
         const char *src[K::PW];
 #pragma unroll
@@ -633,7 +636,7 @@ __global__ __launch_bounds__(kSkThreads) void l1sk(const TT *__restrict__ T, int
         }
         AMS_WAIT_VM(0);
 
-        sk_store<K::MB>(acc, ks == 0 && ke == S, rid, m0, n0, n_u, H, b1, keep_z, H1, H1b, H1lo,
+        sk_store<K::MB>(acc, ks == 0 && ke == S, rid, m0, n0, n_u, H, b1s, keep_z, H1, H1b, H1lo,
                         pbuf + ((size_t)w * 2 + (first ? 0 : 1)) * K::TILE, lane, wave);
         first = false;
         it += n;
@@ -942,12 +945,6 @@ __global__ __launch_bounds__(rs::kThreads) __attribute__((amdgpu_waves_per_eu(rs
 // rounding: H1's error against float64 at 12900 rows 1.7e-7 (5.4e-7 with one
 // accumulator, 4.6e-7 in float32 MFMA), dW1's 2.0e-7 (4.3e-7), in the same time.
 
-__device__ __forceinline__ uint32_t cvt_pk_bf16(float a, float b)
-{
-    const bf16x2 v = {(__bf16)a, (__bf16)b};      // round to nearest even
-    return __builtin_bit_cast(uint32_t, v);
-}
-
 // x[0..7] -> the three bf16x8 parts (element e in bits 16 e .. 16 e + 15)
 __device__ __forceinline__ void split3x8(const float (&x)[8], uint4 &h, uint4 &m, uint4 &l)
 {
@@ -1055,6 +1052,7 @@ __global__ __launch_bounds__(kSkThreads) void l1sk_x3(const float *__restrict__ 
     __shared__ __attribute__((aligned(16))) float ring0[X3::SLOT];
     __shared__ __attribute__((aligned(16))) float ring1[X3::SLOT];
     __shared__ int rid[X3::BM];
+    __shared__ __attribute__((aligned(16))) float b1s[kSkBN];
 
     const int n_u = min(*n_uniq_p, cap);
     if (n_u <= 0) return;
@@ -1080,6 +1078,7 @@ __global__ __launch_bounds__(kSkThreads) void l1sk_x3(const float *__restrict__ 
             }
             rid[t] = id;
         }
+        if (t >= kSkThreads - kSkBN && ks == 0 && ke == S) b1s[t - (kSkThreads - kSkBN)] = b1[n0 + t - (kSkThreads - kSkBN)];
         __syncthreads();
         const char *src[X3::PW];
 #pragma unroll
@@ -1135,7 +1134,7 @@ __global__ __launch_bounds__(kSkThreads) void l1sk_x3(const float *__restrict__ 
         AMS_WAIT_VM(0);
 #pragma unroll
         for (int nb = 0; nb < kSkNB; ++nb) acc[0][nb] += low[nb];
-        sk_store<1>(acc, ks == 0 && ke == S, rid, m0, n0, n_u, H, b1, keep_z, H1, nullptr, nullptr,
+        sk_store<1>(acc, ks == 0 && ke == S, rid, m0, n0, n_u, H, b1s, keep_z, H1, nullptr, nullptr,
                     pbuf + ((size_t)w * 2 + (first ? 0 : 1)) * X3::TILE, lane, wave);
         first = false;
         it += n;
