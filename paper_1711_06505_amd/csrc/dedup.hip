@@ -238,7 +238,8 @@ __global__ __launch_bounds__(kThreads) void dd_zero(uint32_t *__restrict__ words
 // A batch this small is bound by launches.  IDs of 18 bits, whole call: 576
 // occurrences 24.0 us in five launches, 8.6 us so; 2000: 26.6 and 9.6; 4000:
 // 32.8 and 14.5; 8000: 33.0 and 23.1 (one compute unit ranks 8192 keys in the
-// time five launches take for 16384, hence the line at 8192).
+// time five launches take for 16384, hence the line at 8192).  At 31 bits, four
+// passes: 2048 37.8 and 12.5; 8192 48.3 and 32.7, with 44.8 in tiles at 8193.
 constexpr int kSmallThreads = 1024;
 constexpr int kSmallWaves = kSmallThreads / AMS_WAVE;
 constexpr int kSmallMax = 8 * kSmallThreads;
@@ -711,7 +712,8 @@ constexpr int id_bits(int32_t n_ids)
 constexpr int64_t kWideOcc = 1 << 20;
 constexpr int kWideRows = 2 * kRows;
 // From kBucketOcc on, while the buckets are enough, the inverse index goes by
-// buckets; their counters follow the histograms.
+// buckets; their counters follow the histograms.  Past 2^24 occurrences there are
+// not, and the random stores come back (2M IDs: 506 us at 2^24, 638 past it).
 constexpr int64_t kBucketOcc = 1 << 21;
 static_assert(kMaxPasses * kRadix + kMaxBuckets * kBucketStride <= kPrepBlocks * kMaxPasses * kRadix &&
                   kBucketOcc >= kWideOcc && kWideOcc >= kPrepBlocks * kTile,

@@ -96,8 +96,8 @@ __device__ __forceinline__ void dma16(const void *src, void *dst)
 
 // A gather of one row per lane.  Read with one lane per row, each 16-byte load
 // touches 64 lines, and the vector memory pipeline returns about one of them
-// every two cycles (its data unit was busy 90 % of the stable-order pass that
-// read its rows so).  So LPR lanes read one packed row of 4 LPR floats,
+// every two cycles (its data unit is busy 93 % of the stable-order pass that
+// reads its rows so).  So LPR lanes read one packed row of 4 LPR floats,
 // 64 / LPR rows per load, straight into LDS, and each lane takes its own from
 // there.  Lane l's row starts at 4 LPR l floats; its piece p lies at
 // p ^ row_swz(l), which spreads a quarter-wave's reads over the banks.
@@ -593,10 +593,10 @@ __device__ __forceinline__ void seg_sums(int u, bool valid, float (&v)[DM], int 
 // same values; use_packed says which.
 //
 // Packed rows by way of LDS.  Bound by lines: a position's record is 16 bytes of
-// a line of its own, and past the L2's 4 MB its sample's row is another (12.07M
-// positions, 65536 samples, attention: 18M lines of 128 bytes, 319 us = 7.2
-// TB/s; each row where it is 443 us.  752k positions 26.9 -> 23.8 us, 2.2M 77.5
-// -> 54.2).  One chunk per wave: two hold twice the LDS, so no more are in
+// a line of its own, and past the L2's 4 MB its sample's row is another (12.14M
+// positions, 65536 samples, attention: 18.2M reads of 128 bytes, 319 us = 7.3
+// TB/s, with the data unit busy 96 % of it; each row where it is 23.0M reads, 443
+// us, 93 %).  One chunk per wave: two hold twice the LDS, so no more are in
 // flight (341 us).
 template <int MODE, int DM>
 __global__ __launch_bounds__(kThreads) void pool_bwd_seg(int D, int n_occ, int cap,
