@@ -354,10 +354,12 @@ struct Pack {
 //   sum        D=4 16384x183 85/80, 65536x183 264/310 (rows of 16 bytes stay in
 //              the L2); D=8 16384x183 89/81, 65536x183 296/315; D=10 20000x10
 //              27/29, 65536x10 57/52; D=12 50000x1 22/28, 16384x60 46/46,
-//              65536x60 134/126; D=16 16384x60 55/52, 20000x10 28/30
+//              65536x60 134/126; D=16 16384x60 55/52, 20000x10 28/30; D=29
+//              21629x17 131/112, 4332x22 48/46
 //   max        D=4 65536x60 119/140; D=8 20000x10 26/30, 4096x183 41/39; D=12
 //              50000x1 25/29, 20000x30 48/40, 65536x183 485/362; D=20 8192x15
-//              30/33, 4096x60 41/40
+//              30/33, 4096x60 41/40; D=32 4096x20 34/29, 50000x1 41/43; D=27
+//              637x42 42/41
 //   attention  (where the per-sample pass reads the rows anyway) D=1 65536x183
 //              388/437; D=4 16384x60 56/59, 16384x183 120/109; D=12 4096x20
 //              21/21, 20000x10 41/39, 65536x183 610/496; D=13 4096x8 21/19; D=20
@@ -372,14 +374,18 @@ bool use_packed(int B, int64_t n_beh, int D)
     if (MODE == kPoolConcat) return false;
     auto lists = [&](int mean, int64_t n) { return n_beh >= n && n_beh >= (int64_t)mean * B; };
     const int64_t many = 150000, half_m = 1 << 19, m = 1 << 20;
-    const int pieces = (P::two ? 2 : 1) * (D % 4 == 0 ? D / 4 : D);
+    const int row = D % 4 == 0 ? D / 4 : D, pieces = !P::two ? row : MODE == AMS_POOL_MAX ? row + D : 2 * row;
     const bool ragged = pieces >= 2 * P::lpr, wide = 8 * pieces >= 7 * P::lpr;
     if (MODE == AMS_POOL_SUM) {
         if (D <= 8) return lists(100, m) && B <= 16384;
+        if (pieces >= 3 * P::lpr) return lists(8, 20000);
         if (ragged) return lists(20, many) || lists(10, half_m);
         return wide ? lists(10, half_m) : lists(40, m);
     }
-    if (MODE == AMS_POOL_MAX) return D > 8 ? lists(10, many) : D > 4 && lists(25, half_m);
+    if (MODE == AMS_POOL_MAX) {
+        if (D <= 8) return D > 4 && lists(25, half_m);
+        return ragged ? lists(8, 20000) : lists(10, many);
+    }
     if (D <= 4) return D > 2 && lists(100, m);
     if (ragged) return true;
     if (DM <= 16 || wide) return B <= 1024 || lists(10, many);
