@@ -334,7 +334,7 @@ constexpr bool wide_rec() { return MODE == AMS_POOL_ATT || MODE == kPoolQuery; }
 // (sum), and beside it the query row (attention), the argmax positions (max).
 // An ad's are [dA | the attention term da], or [dA | its own position], so that
 // one rule makes both kinds' gradients.  A row is whole 16-byte pieces within
-// whole cache lines: the stable-order pass reads it with kLpr lanes.
+// whole cache lines: the stable-order pass reads it with lpr lanes.
 template <int MODE, int DM>
 struct Pack {
     static constexpr bool two = MODE != AMS_POOL_SUM && MODE != kPoolConcat;
